@@ -19,13 +19,14 @@
 // chains over the float32 summaries, ranked by wave_top_k, one wave per row
 // (larger score first, lower index on ties; sets returned ascending).
 //
-// Attention: one workgroup of four waves per (query row, kv head), all G
-// query heads together. A single query row is no dense contraction, so the
-// work stays on the vector units: lane = key for the scores (each lane reads
-// its key's K and V rows), an online softmax with wave-uniform maxima, and
-// lane = head-dim slice for P.V over the tile's V rows staged in LDS. The
-// four waves take every fourth 64-key tile of the routed set and merge their
-// partial softmax states at the end.
+// Attention, bf16: rows of one block in groups of up to 16 (row, query head)
+// pairs on the matrix cores (attend_rows_fwd_mfma_kernel below).
+// Attention, float32: one workgroup of four waves per (query row, kv head),
+// all G query heads together, on the vector units: lane = key for the scores
+// (each lane reads its key's K and V rows), an online softmax with
+// wave-uniform maxima, and lane = head-dim slice for P.V over the tile's V
+// rows staged in LDS. The four waves take every fourth 64-key tile of the
+// routed set and merge their partial softmax states at the end.
 #include "route_device.h"
 
 namespace hga {
@@ -463,171 +464,455 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
   }
 }
 
-// bf16: the scores and P.V on the matrix cores, with the 4x4x4 product that
-// computes sixteen independent 4 x 4 blocks per instruction
-// (v_mfma_f32_4x4x4_16b_bf16): lanes 4b .. 4b+3 hold block b; lane 4b+i gives
-// row i of A and lane 4b+j column j of B (four k values each), and lane 4b+j
-// receives column j of the block's 4 x 4 result.
-//  - S: the query heads are the rows of A (four per product, zero rows past
-//    G), the keys the columns of B (lane = key, its own K row) and the head
-//    dim the k axis: lane = key receives its key's score for four heads, the
-//    layout the softmax below works in.
-//  - P.V: the heads are again the rows (P from LDS, rounded to bf16 as in
-//    the block kernels' P.V), the tile's keys the k axis, and the head dim
-//    the columns: sixteen blocks of four columns per product, B read from the
-//    row-major V tile with the LDS transpose load. Lane l receives column
-//    64 dh + l of O for four heads.
-template <int D, int G>
-__global__ __launch_bounds__(256) void attend_rows_fwd_mfma_kernel(AttnArgs a) {
-  constexpr int NG = (G + 3) / 4;  // four-head row groups of A
-  constexpr int GR = 4 * NG;       // rows of A (heads past G are zero)
-  constexpr int NP = D * 2 / 16;   // 16-byte pieces of a key row
-  constexpr int NKS = D / 4;       // k steps of S
-  constexpr int NDH = D / 64;      // 64-column slices of O
-  constexpr int VP = D * 2 + 16;   // LDS pitch of a staged V row (padded against bank conflicts)
-  __shared__ __attribute__((aligned(16))) uint16_t s_q[GR][D];      // bf16 query rows of the G heads
-  __shared__ __attribute__((aligned(16))) uint16_t s_p[4][GR][64];  // each wave's P, bf16, [head][key]
-  __shared__ float s_m[4][G], s_l[4][G];
-  // each wave's current half tile of V rows (32 keys), row = key; after the
-  // tiles, its partial O (about 38 KB of LDS in all: three workgroups per CU)
-  __shared__ __attribute__((aligned(16))) char s_v[4][32 * VP];
-  static_assert(G * D * 4 <= 32 * VP, "a wave's partial O fits its V buffer");
+// bf16: rows in groups, scores and P.V on the matrix cores.
+//
+// A group is RPW consecutive rows at positions RPW * i .. (RPW divides 64: one
+// block, one set of windows), at most 16 (row, query head) pairs, the columns
+// of the 16 x 16 x 32 products. Its key lists are walked 32 keys at a time:
+// first the shared one (sink window, local window up to the group's last
+// row), every row at once; then each row's private one (its selected groups),
+// in the same products with the other rows' columns computed and dropped. The
+// columns are 3/4 idle there, which costs little: the kernel is bound by the
+// gathered bytes, and by how they are gathered.
+//  - Loads: consecutive lanes take consecutive 16-byte pieces of a row (four
+//    rows of 256 bytes per instruction) and the rows go through LDS. With one
+//    lane per key, or with each lane its operand's piece, neighbouring lanes
+//    lie in different rows: every lane is then a cache access of its own, and
+//    the issue of the loads took longer than all else.
+//  - S^T = K Q^T: K rows from LDS (A operand), the pairs' Q rows in registers.
+//  - online softmax: lane l holds 8 scores of pair l % 16; the maximum over
+//    the four lanes of a pair goes by lane swaps.
+//  - O^T += V^T P^T: P^T from the registers that hold S^T (bf16), V from LDS
+//    through the transpose load.
+// One register set of K and one of V: the next step's rows go out when these
+// are in LDS (one buffer per wave, K and then V).
+//
+// KW == 1: a wave per group, four groups per workgroup. KW > 1 (few rows):
+// the KW waves of a workgroup take every KW-th step of one group's lists and
+// merge their softmax states through LDS.
+//
+// Strictly causal 1,024-row segment at 16K (Qwen3-8B layer): 172 us with one
+// workgroup per row and one lane per key, 50 us so; a decode step at 16K 9.6 and
+// 7.1 us.
+constexpr int kRowsStep = 32;  // keys of a step
+// Which form a call takes, by its (group, kv head) and (row, kv head) pairs.
+// Qwen3-8B layer, 320 keys a row: 256 rows (512 group pairs) take 27.8 us with
+// a wave per group and 19.2 with four, 512 rows 29.9 and 33.7, 1,024 rows 50
+// and 61; 32 rows (256 pairs) take 12.3 us with four waves per group of rows
+// and 8.2 with twelve per row, 64 rows 12.7 and 14.7.
+constexpr int64_t kRowsWaveGroups = 1024, kRowsSplitPairs = 512;
+
+// Swaps the odd 16-lane rows of x with the even rows of y (or the upper half
+// of x with the lower half of y): with y a copy of x the two then hold, in
+// every lane, its own value and that of lane ^ 16 (^ 32), in some order. (As
+// asm with two operands of its own: the builtin with one value for both
+// gives one register for both results. The wait states are the ones that a
+// lane swap needs after a vector write.)
+__device__ inline void swap16(float& x, float& y) { asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y)); }
+__device__ inline void swap32(float& x, float& y) { asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y)); }
+
+// Maximum and sum over the four lanes l % 16 + 16 i, the same in each.
+__device__ inline float quad_max(float x) {
+  float y = x;
+  swap16(x, y);
+  x = y = fmaxf(x, y);
+  swap32(x, y);
+  return fmaxf(x, y);
+}
+__device__ inline float quad_sum(float x) {
+  float y = x;
+  swap16(x, y);
+  x = y = x + y;
+  swap32(x, y);
+  return x + y;
+}
+
+// A group of rows and its key lists. List 0 is shared (n_sh keys: the sink
+// window, then the local window up to the last row; a row takes those up to
+// its own position); list 1 + r is row r's: its selected groups.
+struct RowGroup {
+  int64_t pos0;   // position of the first row
+  int64_t row0;   // its row in the call
+  int nr;         // rows
+  int64_t ls;     // local window start
+  int ns;         // sink tokens
+  int n_sh;       // keys of the shared list
+  int gshift;
+  int cnt;        // lane r: tokens of row r's selected groups
+  const int* sel; // this wave's LDS [row][64]: selected group ids
+
+  // Keys of list u (u the same in every lane), and the steps they take.
+  __device__ inline int len(int u) const {
+    return u == 0 ? n_sh : __builtin_amdgcn_readlane(cnt, u - 1);
+  }
+  __device__ inline int steps(int u) const { return (len(u) + kRowsStep - 1) / kRowsStep; }
+  // Tokens of keys p, p + dp, ... of list u (clamped to the list). The list
+  // is chosen once, so that the reads of the selected ids go out together.
+  template <int N>
+  __device__ inline void tokens(int u, int p, int dp, uint32_t (&t)[N]) const {
+    if (u == 0) {
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const int q = min(p + dp * j, n_sh - 1);
+        t[j] = (uint32_t)q + (q < ns ? 0u : (uint32_t)ls - (uint32_t)ns);
+      }
+    } else {
+      const int last = __builtin_amdgcn_readlane(cnt, u - 1) - 1;
+      const int* s = sel + (u - 1) * 64;
+#pragma unroll
+      for (int j = 0; j < N; ++j) t[j] = (uint32_t)s[min(p + dp * j, last) >> gshift];
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        t[j] = (t[j] << gshift) + ((uint32_t)min(p + dp * j, last) & ((1u << gshift) - 1u));
+    }
+  }
+};
+
+// The group of `nr` rows of the call from row `row0` on (all in one block),
+// without its selected groups (cnt).
+__device__ inline RowGroup row_group(const AttnArgs& a, int64_t row0, int nr, const int* s_sel) {
+  RowGroup g;
+  g.row0 = row0;
+  g.pos0 = a.q_begin + row0;
+  g.nr = nr;
+  const int64_t block_end = (g.pos0 / 64 + 1) * 64;
+  g.ls = block_end - a.local_tokens > 0 ? block_end - a.local_tokens : 0;
+  g.ns = (int)min((int64_t)a.sink_tokens, g.ls);
+  g.n_sh = g.ns + (int)(g.pos0 + nr - g.ls);
+  g.gshift = a.group_shift;
+  g.cnt = 0;
+  g.sel = s_sel;
+  return g;
+}
+
+// The routing rows of a group, one entry per lane: requested at the start,
+// taken (to the wave's LDS list) when the windows' loads are out.
+template <int RPW>
+struct RowRoutes {
+  int n;
+  int sel[RPW];
+  __device__ inline void load(const AttnArgs& a, const RowGroup& g, int h, int lane) {
+    n = 0;
+    if (a.top_groups > 0) {
+      // lanes and rows past the end repeat the last entry
+      n = a.n_sel[(g.row0 + min(lane, g.nr - 1)) * a.n_kv_heads + h];
+#pragma unroll
+      for (int r = 0; r < RPW; ++r)
+        sel[r] = a.sel_groups[((g.row0 + min(r, g.nr - 1)) * a.n_kv_heads + h) * a.top_groups +
+                              min(lane, a.top_groups - 1)];
+    }
+  }
+  __device__ inline void take(const AttnArgs& a, RowGroup& g, int* s_sel, int lane) const {
+    g.cnt = n << a.group_shift;
+    if (a.top_groups > 0) {
+#pragma unroll
+      for (int r = 0; r < RPW; ++r) s_sel[r * 64 + lane] = sel[r];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+
+// A step of a walk over the lists of a group: keys [32 f, 32 f + 32) of list
+// u. A wave starts at its index and advances by the number of waves.
+struct RowStep {
+  int u, f, n;  // n: steps of list u
+  __device__ inline void settle(const RowGroup& g) {
+    while (u <= g.nr) {
+      n = g.steps(u);
+      if (f < n) return;
+      f -= n;
+      ++u;
+    }
+  }
+};
+
+// One lane's share of a step's 32 rows of K or V: 16-byte pieces, a row's
+// pieces on consecutive lanes; their tokens serve both tensors.
+template <int D>
+struct RowRegs {
+  static constexpr int PPR = D / 8;         // pieces of a row
+  static constexpr int RPI = 64 / PPR;      // rows per load instruction
+  static constexpr int NJ = kRowsStep / RPI;
+  u32x4 x[NJ];
+  static __device__ inline void tokens(const RowGroup& g, const RowStep& st, int lane, uint32_t (&t)[NJ]) {
+    g.tokens(st.u, kRowsStep * st.f + lane / PPR, RPI, t);
+  }
+  __device__ inline void load(const char* base, int64_t stride, const uint32_t (&t)[NJ], int lane) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      x[j] = *reinterpret_cast<const u32x4*>(row_ptr(base, t[j], stride) + 16 * (lane % PPR));
+  }
+  __device__ inline void store(char* dst, int pitch, int lane) const {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      *reinterpret_cast<u32x4*>(dst + (RPI * j + lane / PPR) * pitch + 16 * (lane % PPR)) = x[j];
+  }
+};
+
+template <int D, int G, int RPW, int KW>
+__global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void attend_rows_fwd_mfma_kernel(AttnArgs a, int64_t n_rows,
+                                                                                      int64_t n_groups) {
+  constexpr int NS = D / 32;       // k steps of S
+  constexpr int NT = D / 16;       // 16-row tiles of O^T
+  constexpr int KP = D * 2 + 16;   // LDS pitch of a K row: an operand read's sixteen rows start 4 banks apart
+  constexpr int VP = D * 2 + 32;   // and of a V row: a transpose load's eight rows start 8 banks apart
+  constexpr int NW = KW == 1 ? 4 : KW;
+  constexpr int NG = KW == 1 ? 4 : 1;  // groups per workgroup
+  static_assert(RPW * G <= 16, "a group's pairs are the columns of one product");
+  // each wave's K, then V rows of its current step; with KW > 1, at the end, its O
+  __shared__ __attribute__((aligned(16))) char s_v[NW][kRowsStep * VP];
+  __shared__ int s_sel[NW][RPW * 64];
+  __shared__ float s_m[NW][16], s_l[NW][16];
+  __shared__ int s_bad[NW];
+  static_assert(16 * D * 4 <= kRowsStep * VP, "a wave's partial O fits its V buffer");
   typedef __attribute__((address_space(3))) s16x4* lds_s4;
+  prefetch_args(a);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x % a.n_kv_heads;
-  const int64_t row = blockIdx.x / a.n_kv_heads;
-  const char* Qb = static_cast<const char*>(a.Q);
-  const char* Kb = static_cast<const char*>(a.K);
-  const char* Vb = static_cast<const char*>(a.V);
-
-  for (int x = tid; x < GR * D; x += 256) {
-    const int g = x / D, e = x % D;
-    s_q[g][e] = g < G ? *reinterpret_cast<const uint16_t*>(Qb + (row * a.q_tok + (int64_t)(h * G + g) * a.q_head + e) * 2)
-                      : (uint16_t)0;
-  }
-  if constexpr (GR > G) {
-    for (int x = tid; x < 4 * (GR - G) * 64; x += 256) s_p[x / ((GR - G) * 64)][G + (x / 64) % (GR - G)][x % 64] = 0;
-  }
-  const RowSet rs = row_set(a, row, h);
-  __syncthreads();
-
-  float m[G], l[G];
-  f32x4 oacc[NG][NDH];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m[g] = -__builtin_inff();
-    l[g] = 0.0f;
-  }
-#pragma unroll
-  for (int ng = 0; ng < NG; ++ng)
-#pragma unroll
-    for (int dh = 0; dh < NDH; ++dh) oacc[ng][dh] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int64_t gi = (int64_t)(blockIdx.x / a.n_kv_heads) * NG + (KW == 1 ? wave : 0);
+  if (KW == 1 && gi >= n_groups) return;  // no barrier follows with KW == 1
+  // rows [r_lo, r_hi) of the call: positions RPW * i .. RPW * i + RPW - 1
+  const int64_t p_lo = (a.q_begin / RPW + gi) * RPW - a.q_begin;
+  const int64_t r_lo = p_lo > 0 ? p_lo : 0;
+  const int64_t r_hi = min(p_lo + RPW, n_rows);
+  const int pr = lane & 15, quad = lane >> 4;  // this lane's pair (column) and quarter
+  const int hq = h * G + pr % G;
+  const char* Kb = static_cast<const char*>(a.K) + (int64_t)h * a.k_head * 2;
+  const char* Vb = static_cast<const char*>(a.V) + (int64_t)h * a.v_head * 2;
   const int64_t k_stride = a.k_tok * 2, v_stride = a.v_tok * 2;
-  const int64_t k_head = (int64_t)h * a.k_head * 2, v_head = (int64_t)h * a.v_head * 2;
+  const float c = a.scale_log2;
+  const float lazy = 8.0f / c;  // the maximum is raised when it grows by more than 2^8
   char* sv = s_v[wave];
-  uint16_t(*sp)[64] = s_p[wave];
-  for (int tb = wave * 64; tb < rs.R; tb += 256) {
-    const int p = tb + lane;
-    const bool valid = p < rs.R;
-    const int64_t t = row_token(min(p, rs.R - 1), rs.n_sink, rs.n_grp_tok, rs.ls, rs.sel, a.group_shift);
-    const char* kr = row_ptr(Kb, t, k_stride) + k_head;
-    const char* vrow = row_ptr(Vb, t, v_stride) + v_head;
-    u32x4 kw[NP], vw[NP];
+  const char* tr = sv + (4 * quad + (pr >> 2)) * VP + 8 * (pr & 3);  // this lane's transpose-load address
+  char* Ob = static_cast<char*>(a.Out);
+
+  // The rows all at once; then, if an infinity or a NaN came out, each alone:
+  // it may stem from a V row that only some of them attend and that met a
+  // zero weight in the others' columns.
+  int64_t row0 = r_lo;
+  int nr = (int)(r_hi - r_lo);
+  bool alone = nr == 1;
+  for (;;) {
+    RowGroup g = row_group(a, row0, nr, s_sel[wave]);
+    RowRoutes<RPW> routes;
+    routes.load(a, g, h, lane);
+    const int ri = min(pr / G, nr - 1);  // this lane's row in the group (surplus columns repeat the last row)
+    const int64_t row = row0 + ri;
+    bf16x8 qf[NS];
+    {
+      const char* qr = static_cast<const char*>(a.Q) + (row * a.q_tok + (int64_t)hq * a.q_head) * 2;
 #pragma unroll
-    for (int c = 0; c < NP; ++c) kw[c] = *reinterpret_cast<const u32x4*>(kr + 16 * c);
-#pragma unroll
-    for (int c = 0; c < NP; ++c) vw[c] = *reinterpret_cast<const u32x4*>(vrow + 16 * c);
-    // S: this lane's key against the G heads, four heads per product
-    f32x4 sacc[NG];
-#pragma unroll
-    for (int ng = 0; ng < NG; ++ng) sacc[ng] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      const u32x4 pc = kw[ks / 2];
-      const s16x4 kb = __builtin_bit_cast(s16x4, uint2{pc[2 * (ks % 2)], pc[2 * (ks % 2) + 1]});
-#pragma unroll
-      for (int ng = 0; ng < NG; ++ng) {
-        const s16x4 qa = *reinterpret_cast<const s16x4*>(&s_q[4 * ng + (lane & 3)][4 * ks]);
-        sacc[ng] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(qa, kb, sacc[ng], 0, 0, 0);
-      }
+      for (int s = 0; s < NS; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qr + 64 * s + 16 * quad);
     }
-    // online softmax in log2 units; the maximum is uniform over the wave
-    float pr[G];
+    // with few rows the routing and query rows go ahead of every wave's K and V rows
+    if constexpr (KW > 1) __builtin_amdgcn_s_barrier();
+
+    // this lane's pair: running maximum (raw scores), sum, O
+    float m = -__builtin_inff(), l = 0.0f;
+    f32x4 o[NT];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float sg = valid ? sacc[g / 4][g % 4] * a.scale_log2 : -__builtin_inff();
-      const float mn = fmaxf(m[g], wave_max(sg));
-      const float alpha = exp2f(m[g] - mn);
-      pr[g] = exp2f(sg - mn);
-      l[g] = l[g] * alpha + pr[g];
-#pragma unroll
-      for (int dh = 0; dh < NDH; ++dh) oacc[g / 4][dh][g % 4] *= alpha;
-      m[g] = mn;
-    }
-    // P (bf16) and the tile's V rows through LDS
-#pragma unroll
-    for (int g = 0; g < G; ++g) sp[g][lane] = (uint16_t)float_to_bf16_bits(pr[g]);
-    // P.V over the tile's 64 keys in two halves of 32, each half's V rows
-    // staged by its own lanes, four keys per k step
-    const int i = lane & 15, col0 = 16 * (lane >> 4) + 4 * (i & 3);
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
-      if ((lane >> 5) == hf) {
-#pragma unroll
-        for (int c = 0; c < NP; ++c) *reinterpret_cast<u32x4*>(sv + (lane & 31) * VP + 16 * c) = vw[c];
+    for (int t = 0; t < NT; ++t) o[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // one step, its rows in kr and vr, which refill with the rows of step `ld`
+    auto step = [&](const RowStep& st, RowRegs<D>& kr, RowRegs<D>& vr, const RowStep& ld,
+                    bool more) __attribute__((always_inline)) {
+      kr.store(sv, KP, lane);
+      uint32_t tok[RowRegs<D>::NJ];
+      if (more) {
+        RowRegs<D>::tokens(g, ld, lane, tok);
+        kr.load(Kb, k_stride, tok, lane);
       }
       __builtin_amdgcn_wave_barrier();
-#pragma unroll 4
-      for (int k8 = 0; k8 < 8; ++k8) {
-        const int kk = 8 * hf + k8;
-        s16x4 pa[NG];
+      f32x4 s[2];
 #pragma unroll
-        for (int ng = 0; ng < NG; ++ng) pa[ng] = *reinterpret_cast<const s16x4*>(&sp[4 * ng + (lane & 3)][4 * kk]);
+      for (int t = 0; t < 2; ++t) {
+        s[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int dh = 0; dh < NDH; ++dh) {
-          const s16x4 vb = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (lds_s4)(sv + (4 * k8 + (i >> 2)) * VP + (64 * dh + col0) * 2));
+        for (int k = 0; k < NS; ++k)
+          s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              *reinterpret_cast<const bf16x8*>(sv + (16 * t + pr) * KP + 64 * k + 16 * quad), qf[k], s[t], 0, 0, 0);
+      }
+      __builtin_amdgcn_wave_barrier();
+      vr.store(sv, VP, lane);
+      if (more) vr.load(Vb, v_stride, tok, lane);
+      // this lane's keys of the list are [0, last): in the shared list those
+      // up to its row, in a row's list all or, in other rows' columns, none
+      const int last = st.u == 0 ? g.n_sh - (nr - 1) + ri : ri == st.u - 1 ? g.len(st.u) : 0;
+      const int end = kRowsStep * (st.f + 1);
+      if (st.u > 0 || end > g.n_sh - (nr - 1)) {
 #pragma unroll
-          for (int ng = 0; ng < NG; ++ng) oacc[ng][dh] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(pa[ng], vb, oacc[ng][dh], 0, 0, 0);
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (end - kRowsStep + 16 * t + 4 * quad + i >= last) s[t][i] = -__builtin_inff();
+      }
+      float mx = -__builtin_inff();
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[t][i]);
+      mx = quad_max(mx);
+      const bool raise = mx > m + lazy;
+      if (__any(raise)) {
+        const float mn = raise ? mx : m;
+        const float corr = m == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f((m - mn) * c);
+        if (raise) {
+          m = mn;
+          l *= corr;
+        }
+        const float f = raise ? corr : 1.0f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) o[t] *= f;
+      }
+      const float mc = m == -__builtin_inff() ? 0.0f : m * c;  // nothing attended yet: every p is 0
+      bf16x8 pf;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[t][i], c, -mc));
+          l += p;
+          pf[4 * t + i] = (__bf16)p;
+        }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(tr + 32 * t));
+        const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(tr + 16 * VP + 32 * t));
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        const s16x8 xy = __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
+        o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xy), pf, o[t], 0, 0, 0);
+      }
+      __builtin_amdgcn_wave_barrier();
+    };
+    // a wave that starts in the windows does not wait for the routing rows
+    RowStep s0{0, KW == 1 ? 0 : wave, g.steps(0)};
+    RowRegs<D> k0, v0;
+    const bool early = s0.f < s0.n;
+    uint32_t tok0[RowRegs<D>::NJ];
+    if (early) {
+      RowRegs<D>::tokens(g, s0, lane, tok0);
+      k0.load(Kb, k_stride, tok0, lane);
+      v0.load(Vb, v_stride, tok0, lane);
+    }
+    routes.take(a, g, s_sel[wave], lane);
+    s0.settle(g);
+    if (!early && s0.u <= nr) {
+      RowRegs<D>::tokens(g, s0, lane, tok0);
+      k0.load(Kb, k_stride, tok0, lane);
+      v0.load(Vb, v_stride, tok0, lane);
+    }
+    while (s0.u <= nr) {
+      RowStep nx = s0;
+      nx.f += KW;
+      nx.settle(g);
+      // past the end a wave of many steps loads its last rows again, unused:
+      // with conditional loads the compiler waits for both register sets at
+      // each use; a wave of few steps does without them
+      const bool more = nx.u <= nr;
+      const RowStep ld = RowStep{more ? nx.u : s0.u, more ? nx.f : s0.f, more ? nx.n : s0.n};
+      step(s0, k0, v0, ld, KW == 1 || more);
+      s0 = nx;
+    }
+    l = quad_sum(l);
+    bool bad = false;  // a result of the pass is not finite
+    if (!alone) {
+      float sum = l;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) sum += (o[t][0] + o[t][1]) + (o[t][2] + o[t][3]);
+      bad = __any(!(fabsf(sum) < __builtin_inff())) != 0;
+    }
+    if constexpr (KW == 1) {
+      if (!bad && pr < nr * G) {
+        const float inv = 1.0f / l;
+        if (quad == 0) a.lse[row * a.n_q_heads + hq] = (m * c + __log2f(l)) * kLn2;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int d0 = 16 * t + 4 * quad;
+          const f32x4 v = o[t] * inv;
+          *reinterpret_cast<uint2*>(Ob + (row * a.out_tok + (int64_t)hq * a.out_head + d0) * 2) =
+              uint2{float_to_bf16_bits(v[0]) | (float_to_bf16_bits(v[1]) << 16),
+                    float_to_bf16_bits(v[2]) | (float_to_bf16_bits(v[3]) << 16)};
+          if (a.o32) *reinterpret_cast<f32x4*>(a.o32 + (row * a.n_q_heads + hq) * D + d0) = v;
         }
       }
-      __builtin_amdgcn_wave_barrier();
+    } else {
+      float* so = reinterpret_cast<float*>(sv);
+      if (quad == 0) {
+        s_m[wave][pr] = m;
+        s_l[wave][pr] = l;
+      }
+      if (RPW > 1 && lane == 0) s_bad[wave] = bad;
+      if (pr < RPW * G) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4*>(so + pr * D + 16 * t + 4 * quad) = o[t];
+      }
+      __syncthreads();
+      if constexpr (RPW > 1) {
+        bad = false;
+#pragma unroll
+        for (int w = 0; w < KW; ++w) bad |= __builtin_amdgcn_readfirstlane(s_bad[w]) != 0;
+      }
+      for (int x = tid; !bad && x < nr * G * (D / 4); x += 64 * KW) {
+        const int p = x / (D / 4), d0 = 4 * (x % (D / 4));
+        float M = -__builtin_inff();
+#pragma unroll
+        for (int w = 0; w < KW; ++w) M = fmaxf(M, s_m[w][p]);
+        f32x4 num = {0.0f, 0.0f, 0.0f, 0.0f};
+        float den = 0.0f;
+#pragma unroll
+        for (int w = 0; w < KW; ++w) {
+          const float f = s_m[w][p] == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f((s_m[w][p] - M) * c);
+          num += f * *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(s_v[w]) + p * D + d0);
+          den = fmaf(f, s_l[w][p], den);
+        }
+        const f32x4 v = num * (1.0f / den);
+        const int64_t r = row0 + p / G;
+        const int hp = h * G + p % G;
+        *reinterpret_cast<uint2*>(Ob + (r * a.out_tok + (int64_t)hp * a.out_head + d0) * 2) =
+            uint2{float_to_bf16_bits(v[0]) | (float_to_bf16_bits(v[1]) << 16),
+                  float_to_bf16_bits(v[2]) | (float_to_bf16_bits(v[3]) << 16)};
+        if (a.o32) *reinterpret_cast<f32x4*>(a.o32 + (r * a.n_q_heads + hp) * D + d0) = v;
+        if (d0 == 0) a.lse[r * a.n_q_heads + hp] = (M * c + __log2f(den)) * kLn2;
+      }
+      if constexpr (RPW > 1) __syncthreads();  // the buffers are read: a further pass may overwrite them
+    }
+    // the next pass: the first row alone, then the one after it, ...
+    if constexpr (RPW == 1) {
+      return;
+    } else {
+      if (alone ? row0 + 1 == r_hi || nr == (int)(r_hi - r_lo) : !bad) return;
+      row0 = alone ? row0 + 1 : r_lo;
+      alone = true;
+      nr = 1;
     }
   }
-  // merge the four waves' partial softmax states; a wave's O goes to its own
-  // V buffer, which only it has used
-  float* so = reinterpret_cast<float*>(sv);
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const float lt = wave_sum(l[g]);
-    if (lane == 0) {
-      s_m[wave][g] = m[g];
-      s_l[wave][g] = lt;
-    }
-#pragma unroll
-    for (int dh = 0; dh < NDH; ++dh) so[g * D + 64 * dh + lane] = oacc[g / 4][dh][g % 4];
+}
+
+// Rows per group with several rows: four, two where a row has eight heads.
+template <int G>
+constexpr int rows_per_group() { return G >= 8 ? 2 : 4; }
+
+// Groups of `rpw` rows by position that hold a row of the call.
+static int64_t n_row_groups(const AttnArgs& a, int64_t n_rows, int rpw) {
+  return (a.q_begin + n_rows + rpw - 1) / rpw - a.q_begin / rpw;
+}
+
+template <int D, int G>
+hipError_t rows_fwd_mfma(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
+  constexpr int R = rows_per_group<G>();
+  const int64_t ng = n_row_groups(a, n_rows, R);
+  if (ng * a.n_kv_heads >= kRowsWaveGroups) {
+    hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, R, 1>), dim3((unsigned)((ng + 3) / 4 * a.n_kv_heads)),
+                       dim3(256), 0, s, a, n_rows, ng);
+  } else if (n_rows * a.n_kv_heads >= kRowsSplitPairs) {
+    hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, R, 4>), dim3((unsigned)(ng * a.n_kv_heads)), dim3(256), 0,
+                       s, a, n_rows, ng);
+  } else {
+    hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, 1, 12>), dim3((unsigned)(n_rows * a.n_kv_heads)),
+                       dim3(768), 0, s, a, n_rows, n_rows);
   }
-  __syncthreads();
-  char* Ob = static_cast<char*>(a.Out);
-  for (int x = tid; x < G * D; x += 256) {
-    const int g = x / D, e = x % D;
-    float M = -__builtin_inff();
-#pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, s_m[w][g]);
-    float num = 0.0f, den = 0.0f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float f = s_m[w][g] == -__builtin_inff() ? 0.0f : exp2f(s_m[w][g] - M);
-      num = fmaf(f, reinterpret_cast<const float*>(s_v[w])[g * D + e], num);
-      den = fmaf(f, s_l[w][g], den);
-    }
-    const float out = num / den;
-    char* op = Ob + (row * a.out_tok + (int64_t)(h * G + g) * a.out_head + e) * 2;
-    *reinterpret_cast<uint16_t*>(op) = (uint16_t)float_to_bf16_bits(out);
-    if (a.o32) a.o32[(row * a.n_q_heads + h * G + g) * D + e] = out;
-    if (e == 0) a.lse[row * a.n_q_heads + h * G + g] = (M + log2f(den)) * kLn2;
-  }
+  return hipGetLastError();
 }
 
 template <typename T, int D>
@@ -635,10 +920,10 @@ hipError_t rows_fwd_g(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
   const dim3 grid((unsigned)(n_rows * a.n_kv_heads)), block(256);
   if constexpr (Elem<T>::kBytes == 2) {
     switch (a.gqa) {
-      case 1: hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, 1>), grid, block, 0, s, a); break;
-      case 2: hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, 2>), grid, block, 0, s, a); break;
-      case 4: hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, 4>), grid, block, 0, s, a); break;
-      default: hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, 8>), grid, block, 0, s, a); break;
+      case 1: return rows_fwd_mfma<D, 1>(a, n_rows, s);
+      case 2: return rows_fwd_mfma<D, 2>(a, n_rows, s);
+      case 4: return rows_fwd_mfma<D, 4>(a, n_rows, s);
+      default: return rows_fwd_mfma<D, 8>(a, n_rows, s);
     }
   } else {
     switch (a.gqa) {

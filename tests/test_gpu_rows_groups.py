@@ -1,0 +1,73 @@
+"""Per-query attention on groups of rows (hga_attend_rows_fwd, bf16): the
+three forms a call can take (a wave per group, four waves per group, twelve
+waves per row), with partial first and last groups, for every head ratio; and
+what a row does not attend stays out of its result, infinities and NaN too,
+although the rows of a group share products."""
+
+from dataclasses import replace
+
+import pytest
+import torch
+
+from paper_2607_15105_amd import hga, synth
+from tests import parity as P
+from tests.test_gpu_rows import _gpu, _rows_check  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+# (row, kv head) pairs below 512: twelve waves per row; above, four waves per
+# group, and from 1,024 (group, kv head) pairs a wave per group
+@pytest.mark.parametrize("n_q,q_begin", [(1, 1787), (63, 1500), (66, 1537), (515, 1501)])
+@pytest.mark.parametrize("G,d", [(1, 64), (2, 64), (4, 128), (8, 64)])
+def test_rows_forms(G, d, n_q, q_begin):
+    wl = synth.Workload("rows_forms", T=2048, n_q_heads=8 * G, n_kv_heads=8, head_dim=d, dtype="bf16", seed=31,
+                        q_begin=q_begin, n_q=n_q, grad_begin=0, key_offset="normal", top_groups=13, local_tokens=64)
+    _rows_check(wl, 1)
+
+
+def _fwd(wl, V, x):
+    O = torch.empty_like(x["Q"])
+    lse = torch.empty(wl.n_q, wl.n_q_heads, device="cuda")
+    hga.attend_rows_fwd(x["hc"], x["Q"], x["K"], V, wl.q_begin, x["sg"], x["ns"], O, lse)
+    torch.cuda.synchronize()
+    return O, lse
+
+
+@pytest.mark.parametrize("n_q", [12, 130, 600])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_rows_not_attending_a_non_finite_value_keep_their_result(n_q, bad):
+    """An infinity or a NaN in the V row of a token of the call itself (later
+    rows attend it, earlier rows of its group do not) and of a token that
+    some rows select."""
+    wl = replace(synth.WORKLOADS["qwen3_8b_2k"], q_begin=1410, n_q=n_q)
+    hc = P.hcfg_of(wl)
+    end = wl.q_begin + n_q
+    x = {"hc": hc, "K": P.to_dev(synth.keys(wl, 0, end)), "Q": P.to_dev(synth.queries(wl, wl.q_begin, end))}
+    V = P.to_dev(synth.values(wl, 0, end))
+    cs, gs = hga.alloc_summaries(hc, -(-end // 64) * 64)
+    hga.build_summaries(hc, x["K"], 0, end, cs, gs)
+    sc, x["sg"], x["ns"] = hga.alloc_route_rows(hc, n_q)
+    hga.route_rows(hc, x["Q"], wl.q_begin, cs, gs, sc, x["sg"], x["ns"])
+    O, lse = _fwd(wl, V, x)
+    G, g = wl.n_q_heads // wl.n_kv_heads, wl.group_size
+    own = wl.q_begin + 6                                   # position of row 6
+    sel = int(x["sg"][3, 0, 0])                            # a group that row 3 selects for kv head 0
+    V2 = V.clone()
+    V2[own, :, 1] = bad
+    V2[sel * g + 1, 0, 5] = bad
+    O2, lse2 = _fwd(wl, V2, x)
+    rows = torch.arange(n_q, device="cuda")
+    blk = (wl.q_begin + rows) // 64 * 64 + 64
+    sees_own = ((rows >= 6) & (own >= blk - wl.local_tokens))[:, None] | (x["sg"] == own // g).any(-1)
+    sees_sel = (x["sg"] == sel).any(-1)
+    sees_sel[:, 1:] = False
+    assert (sel + 1) * g <= wl.q_begin - 127               # outside every row's windows
+    clean = ~(sees_own | sees_sel)
+    assert clean[:6].any() and sees_sel[:6, 0].any() and (n_q < 100 or clean[100:].any())
+    o, o2 = (t.float().view(n_q, wl.n_kv_heads, G, -1) for t in (O, O2))
+    assert torch.isfinite(o2[clean]).all()
+    assert (o - o2)[clean].abs().max() <= 2 ** -8 * o[clean].abs().max()
+    assert not torch.isfinite(o2[..., 1][sees_own]).any()
+    assert not torch.isfinite(o2[..., 5][sees_sel]).any()
+    assert (lse - lse2).abs().max() <= 1e-5
