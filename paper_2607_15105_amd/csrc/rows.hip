@@ -943,14 +943,12 @@ hipError_t launch_attend_rows_fwd(const AttnArgs& a, int64_t n_rows, bool bf16, 
 
 // ---------------------------------------------------------------- backward
 //
-// The backward of hga_attend_rows_fwd with the routing held constant, in
-// three launches:
-//   rows_rowdot_kernel  D = rowsum(dO * O) of every (row, query head);
-//   dQ                  query-major: one workgroup per (row, kv head) walks
-//                       the row's routed set in 64-key tiles, recomputes P
-//                       from the LSE, forms dS = P (dP - D) and accumulates
-//                       dQ = scale dS K (rows_dq_mfma_kernel for bf16 on the
-//                       matrix cores, rows_dq_kernel for float32);
+// The backward of hga_attend_rows_fwd with the routing held constant:
+//   dQ                  query-major: the rows' routed sets in tiles, P
+//                       recomputed from the LSE, dS = P (dP - D) and
+//                       dQ = scale dS K. bf16: rows_dq_mfma_kernel, which also
+//                       forms D = rowsum(dO * O); float32: rows_rowdot_kernel
+//                       for D, then rows_dq_kernel;
 //   dK, dV              key-major and deterministic: one workgroup per (16
 //                       keys of a 64-token chunk of the active tokens, kv
 //                       head). It lists, in row order, the rows whose routed
@@ -1132,143 +1130,210 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
   }
 }
 
-// bf16: dQ on the matrix cores with the forward's 4x4x4 products. S = Q K^T
-// and dP = dO V^T take the heads as the rows of A and lane = key as the
-// block column (its own K and V rows), so lane = key receives both for four
-// heads; dS = P (dP - D) goes to LDS as a bf16 hi + lo pair (as in the
-// block kernels), and dQ += dS K takes the tile's keys as the k axis with K
-// read from LDS through the transpose load. Each wave takes every fourth
-// 64-key tile; the four partial dQ are added in wave order at the end.
-template <int D, int G>
-__global__ __launch_bounds__(256) void rows_dq_mfma_kernel(AttnArgs a) {
-  constexpr int NG = (G + 3) / 4;  // four-head row groups of A
-  constexpr int GR = 4 * NG;       // rows of A (heads past G are zero)
-  constexpr int NP = D * 2 / 16;   // 16-byte pieces of a key row
-  constexpr int NKS = D / 4;       // k steps of S and dP
-  constexpr int NDH = D / 64;      // 64-column slices of dQ
-  constexpr int VP = D * 2 + 16;   // LDS pitch of a staged K row (padded against bank conflicts)
-  __shared__ __attribute__((aligned(16))) uint16_t s_q[GR][D];        // bf16 query rows of the G heads
-  __shared__ __attribute__((aligned(16))) uint16_t s_do[GR][D];       // bf16 dO rows of the G heads
-  // each wave's dS as a bf16 hi + lo pair, [head][key]
-  __shared__ __attribute__((aligned(16))) uint16_t s_ds[4][GR][64], s_dl[4][GR][64];
-  __shared__ float s_lse[G], s_dd[G];
-  // each wave's current K tile, row = key; after the tiles, its partial dQ
-  __shared__ __attribute__((aligned(16))) char s_k[4][64 * VP];
-  static_assert(G * D * 4 <= 64 * VP, "a wave's partial dQ fits its K buffer");
+// bf16: dQ (and D = rowsum(dO * O)) on the forward's groups of rows and key
+// lists, with its loads. S^T = K Q^T and dP^T = V dO^T leave, in lane l, eight
+// keys' scores and dP of pair l % 16; P comes from the LSE, dS = P (dP - D)
+// enters dQ^T += K^T dS^T as a bf16 hi + lo pair (as in the block kernels: dQ
+// scales dS by raw key magnitudes), with K read from LDS by rows for S and
+// through the transpose load for dQ. The kernel also forms its rows' D and
+// leaves it in a.dvec for the dK/dV kernel.
+//
+// Strictly causal 1,024-row segment at 16K (Qwen3-8B layer): 255 us (dQ, one
+// workgroup per row, one lane per key) + 8.8 us (D, a kernel of its own)
+// before, 57 us in all so.
+template <int D, int G, int RPW, int KW>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void rows_dq_mfma_kernel(AttnArgs a,
+                                                                                     int64_t n_rows, int64_t n_groups) {
+  using TL = Tile<__bf16, D>;
+  constexpr int NS = D / 32;       // k steps of S and dP
+  constexpr int NT = D / 16;       // 16-row tiles of dQ^T
+  constexpr int TB = kRowsStep * TL::kRowPitch;  // bytes of 32 rows
+  constexpr int NG = KW == 1 ? 4 : 1;            // groups per workgroup
+  static_assert(RPW * G <= 16, "a group's pairs are the columns of one product");
+  static_assert(KW == 1 || KW == 4, "four waves");
+  // each wave's K and V rows of its current step; with KW > 1, at the end, its dQ
+  __shared__ __attribute__((aligned(16))) char s_kv[4][2 * TB];
+  __shared__ int s_sel[4][RPW * 64];
+  __shared__ int s_bad[4];
+  static_assert(16 * D * 4 <= 2 * TB, "a wave's partial dQ fits its buffer");
   typedef __attribute__((address_space(3))) s16x4* lds_s4;
+  prefetch_args(a);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x % a.n_kv_heads;
-  const int64_t row = blockIdx.x / a.n_kv_heads;
-  const char* Kb = static_cast<const char*>(a.K);
-  const char* Vb = static_cast<const char*>(a.V);
-
-  for (int x = tid; x < GR * D; x += 256) {
-    const int g = x / D, e = x % D;
-    const int64_t hq = h * G + g;
-    s_q[g][e] = g < G ? *reinterpret_cast<const uint16_t*>(static_cast<const char*>(a.Q) + (row * a.q_tok + hq * a.q_head + e) * 2)
-                      : (uint16_t)0;
-    s_do[g][e] = g < G ? *reinterpret_cast<const uint16_t*>(static_cast<const char*>(a.dO) + (row * a.do_tok + hq * a.do_head + e) * 2)
-                       : (uint16_t)0;
-  }
-  if constexpr (GR > G) {
-    for (int x = tid; x < 4 * (GR - G) * 64; x += 256)
-      s_ds[x / ((GR - G) * 64)][G + (x / 64) % (GR - G)][x % 64] = s_dl[x / ((GR - G) * 64)][G + (x / 64) % (GR - G)][x % 64] = 0;
-  }
-  if (tid < G) {
-    s_lse[tid] = a.lse[row * a.n_q_heads + h * G + tid] * kLog2e;
-    s_dd[tid] = a.dvec[row * a.n_q_heads + h * G + tid];
-  }
-  const RowSet rs = row_set(a, row, h);
-  __syncthreads();
-
-  f32x4 dq[NG][NDH];
-#pragma unroll
-  for (int ng = 0; ng < NG; ++ng)
-#pragma unroll
-    for (int dh = 0; dh < NDH; ++dh) dq[ng][dh] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int64_t gi = (int64_t)(blockIdx.x / a.n_kv_heads) * NG + (KW == 1 ? wave : 0);
+  if (KW == 1 && gi >= n_groups) return;  // no barrier follows with KW == 1
+  const int64_t p_lo = (a.q_begin / RPW + gi) * RPW - a.q_begin;
+  const int64_t r_lo = p_lo > 0 ? p_lo : 0;
+  const int64_t r_hi = min(p_lo + RPW, n_rows);
+  const int pr = lane & 15, quad = lane >> 4;  // this lane's pair (column) and quarter
+  const int hq = h * G + pr % G;
+  const char* Kb = static_cast<const char*>(a.K) + (int64_t)h * a.k_head * 2;
+  const char* Vb = static_cast<const char*>(a.V) + (int64_t)h * a.v_head * 2;
   const int64_t k_stride = a.k_tok * 2, v_stride = a.v_tok * 2;
-  const int64_t k_head = (int64_t)h * a.k_head * 2, v_head = (int64_t)h * a.v_head * 2;
-  char* sk = s_k[wave];
-  uint16_t(*sds)[64] = s_ds[wave];
-  uint16_t(*sdl)[64] = s_dl[wave];
-  for (int tb = wave * 64; tb < rs.R; tb += 256) {
-    const int p = tb + lane;
-    const bool valid = p < rs.R;
-    const int64_t t = row_token(min(p, rs.R - 1), rs.n_sink, rs.n_grp_tok, rs.ls, rs.sel, a.group_shift);
-    const char* kr = row_ptr(Kb, t, k_stride) + k_head;
-    const char* vrow = row_ptr(Vb, t, v_stride) + v_head;
-    u32x4 kw[NP], vw[NP];
-#pragma unroll
-    for (int c = 0; c < NP; ++c) kw[c] = *reinterpret_cast<const u32x4*>(kr + 16 * c);
-#pragma unroll
-    for (int c = 0; c < NP; ++c) vw[c] = *reinterpret_cast<const u32x4*>(vrow + 16 * c);
-    // S and dP: this lane's key against the G heads, four heads per product
-    f32x4 sacc[NG], pacc[NG];
-#pragma unroll
-    for (int ng = 0; ng < NG; ++ng) sacc[ng] = pacc[ng] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      const u32x4 kc = kw[ks / 2], vc = vw[ks / 2];
-      const s16x4 kb = __builtin_bit_cast(s16x4, uint2{kc[2 * (ks % 2)], kc[2 * (ks % 2) + 1]});
-      const s16x4 vb = __builtin_bit_cast(s16x4, uint2{vc[2 * (ks % 2)], vc[2 * (ks % 2) + 1]});
-#pragma unroll
-      for (int ng = 0; ng < NG; ++ng) {
-        const s16x4 qa = *reinterpret_cast<const s16x4*>(&s_q[4 * ng + (lane & 3)][4 * ks]);
-        const s16x4 da = *reinterpret_cast<const s16x4*>(&s_do[4 * ng + (lane & 3)][4 * ks]);
-        sacc[ng] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(qa, kb, sacc[ng], 0, 0, 0);
-        pacc[ng] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(da, vb, pacc[ng], 0, 0, 0);
-      }
+  const float c = a.scale_log2;
+  char* sk = s_kv[wave];
+  char* sv = sk + TB;
+  const int rd = TL::row_off(pr, 0) + 16 * quad;               // this lane's operand rows (tile 0)
+  const int tr = TL::row_off(4 * quad + (pr >> 2), 4 * (pr & 3));  // and its transpose-load address
+
+  // The rows all at once; then, if an infinity or a NaN came out, each alone
+  // (see the forward; here K rows meet a zero dS).
+  int64_t row0 = r_lo;
+  int nr = (int)(r_hi - r_lo);
+  bool alone = nr == 1;
+  for (;;) {
+    RowGroup g = row_group(a, row0, nr, s_sel[wave]);
+    RowRoutes<RPW> routes;
+    routes.load(a, g, h, lane);
+    const int ri = min(pr / G, nr - 1);  // this lane's row in the group (surplus columns repeat the last row)
+    const int64_t row = row0 + ri;
+    const int64_t rh = row * a.n_q_heads + hq;
+    RowStep s0{0, KW == 1 ? 0 : wave, g.steps(0)};
+    RowRegs<D> kr, vr;
+    uint32_t tok0[RowRegs<D>::NJ];
+    const bool early = s0.f < s0.n;
+    if (early) {
+      RowRegs<D>::tokens(g, s0, lane, tok0);
+      kr.load(Kb, k_stride, tok0, lane);
+      vr.load(Vb, v_stride, tok0, lane);
     }
-    // dS = P (dP - D), P recomputed from the LSE; dQ multiplies dS by raw
-    // keys, whose magnitude is not bounded, so dS is carried as hi + lo
+    bf16x8 qf[NS], df[NS];
+    float dd = 0.0f;
+    {
+      const char* qr = static_cast<const char*>(a.Q) + (row * a.q_tok + (int64_t)hq * a.q_head) * 2;
+      const char* dr = static_cast<const char*>(a.dO) + (row * a.do_tok + (int64_t)hq * a.do_head) * 2;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const float pr = valid ? exp2f(sacc[g / 4][g % 4] * a.scale_log2 - s_lse[g]) : 0.0f;
-      const float ds = pr * (pacc[g / 4][g % 4] - s_dd[g]);
-      const uint32_t hi = float_to_bf16_bits(ds);
-      sds[g][lane] = (uint16_t)hi;
-      sdl[g][lane] = (uint16_t)float_to_bf16_bits(ds - bf16_bits_to_float(hi));
-    }
-#pragma unroll
-    for (int c = 0; c < NP; ++c) *reinterpret_cast<u32x4*>(sk + lane * VP + 16 * c) = kw[c];
-    __builtin_amdgcn_wave_barrier();
-    // dQ += dS K over the tile's 64 keys, four keys per k step
-    const int i = lane & 15, col0 = 16 * (lane >> 4) + 4 * (i & 3);
-#pragma unroll 4
-    for (int kk = 0; kk < 16; ++kk) {
-      s16x4 da[NG], dl[NG];
-#pragma unroll
-      for (int ng = 0; ng < NG; ++ng) {
-        da[ng] = *reinterpret_cast<const s16x4*>(&sds[4 * ng + (lane & 3)][4 * kk]);
-        dl[ng] = *reinterpret_cast<const s16x4*>(&sdl[4 * ng + (lane & 3)][4 * kk]);
+      for (int s = 0; s < NS; ++s) {
+        qf[s] = *reinterpret_cast<const bf16x8*>(qr + 64 * s + 16 * quad);
+        df[s] = *reinterpret_cast<const bf16x8*>(dr + 64 * s + 16 * quad);
       }
+      if (a.o32) {
+        const float* orow = a.o32 + rh * D;
 #pragma unroll
-      for (int dh = 0; dh < NDH; ++dh) {
-        const s16x4 kb = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (lds_s4)(sk + (4 * kk + (i >> 2)) * VP + (64 * dh + col0) * 2));
+        for (int s = 0; s < NS; ++s) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(orow + 32 * s + 8 * quad);
+          const f32x4 y = *reinterpret_cast<const f32x4*>(orow + 32 * s + 8 * quad + 4);
 #pragma unroll
-        for (int ng = 0; ng < NG; ++ng) {
-          dq[ng][dh] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(da[ng], kb, dq[ng][dh], 0, 0, 0);
-          dq[ng][dh] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(dl[ng], kb, dq[ng][dh], 0, 0, 0);
+          for (int e = 0; e < 4; ++e) dd = fmaf((float)df[s][e], x[e], dd);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dd = fmaf((float)df[s][4 + e], y[e], dd);
+        }
+      } else {
+        const char* orow = static_cast<const char*>(a.O) + (row * a.o_tok + (int64_t)hq * a.o_head) * 2;
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const bf16x8 x = *reinterpret_cast<const bf16x8*>(orow + 64 * s + 16 * quad);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) dd = fmaf((float)df[s][e], (float)x[e], dd);
         }
       }
+      dd = quad_sum(dd);
     }
-    __builtin_amdgcn_wave_barrier();
-  }
-  // the four waves' partial dQ, each in its own K buffer, added in wave order
-  float* so = reinterpret_cast<float*>(sk);
+    const float lse2 = a.lse[rh] * kLog2e;
+    if ((KW == 1 || wave == 0) && quad == 0 && pr < nr * G) a.dvec[rh] = dd;
+    routes.take(a, g, s_sel[wave], lane);
+    s0.settle(g);
+    if (!early && s0.u <= nr) {
+      RowRegs<D>::tokens(g, s0, lane, tok0);
+      kr.load(Kb, k_stride, tok0, lane);
+      vr.load(Vb, v_stride, tok0, lane);
+    }
+    f32x4 dq[NT];
 #pragma unroll
-  for (int g = 0; g < G; ++g)
+    for (int t = 0; t < NT; ++t) dq[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    while (s0.u <= nr) {
+      RowStep nx = s0;
+      nx.f += KW;
+      nx.settle(g);
+      const bool more = nx.u <= nr;
+      const RowStep ld = RowStep{more ? nx.u : s0.u, more ? nx.f : s0.f, more ? nx.n : s0.n};
+      // the step's rows to LDS, the next step's requested (unconditionally,
+      // as in the forward)
 #pragma unroll
-    for (int dh = 0; dh < NDH; ++dh) so[g * D + 64 * dh + lane] = dq[g / 4][dh][g % 4];
-  __syncthreads();
-  for (int x = tid; x < G * D; x += 256) {
-    const int g = x / D, e = x % D;
-    float acc = 0.0f;
+      for (int j = 0; j < RowRegs<D>::NJ; ++j) {
+        const int off = TL::row_off(RowRegs<D>::RPI * j + lane / RowRegs<D>::PPR, 8 * (lane % RowRegs<D>::PPR));
+        *reinterpret_cast<u32x4*>(sk + off) = kr.x[j];
+        *reinterpret_cast<u32x4*>(sv + off) = vr.x[j];
+      }
+      uint32_t tok[RowRegs<D>::NJ];
+      RowRegs<D>::tokens(g, ld, lane, tok);
+      kr.load(Kb, k_stride, tok, lane);
+      vr.load(Vb, v_stride, tok, lane);
+      __builtin_amdgcn_wave_barrier();
+      f32x4 s[2], dp[2];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) acc += reinterpret_cast<const float*>(s_k[w])[g * D + e];
-    a.dQ[(row * a.n_q_heads + h * G + g) * D + e] = acc * a.scale;
+      for (int t = 0; t < 2; ++t) {
+        s[t] = dp[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          const int off = rd + 16 * t * TL::kRowPitch + 64 * k;
+          s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(sk + off), qf[k], s[t], 0, 0, 0);
+          dp[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(sv + off), df[k], dp[t], 0, 0, 0);
+        }
+      }
+      // this lane's keys of the list are [0, last) (see the forward)
+      const int last = s0.u == 0 ? g.n_sh - (nr - 1) + ri : ri == s0.u - 1 ? g.len(s0.u) : 0;
+      const int first = kRowsStep * s0.f + 4 * quad;
+      bf16x8 hi, lo;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[t][i], c, -lse2));
+          const float ds = first + 16 * t + i < last ? p * (dp[t][i] - dd) : 0.0f;
+          hi[4 * t + i] = (__bf16)ds;
+          lo[4 * t + i] = (__bf16)(ds - (float)hi[4 * t + i]);
+        }
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(sk + tr + 32 * t));
+        const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(sk + tr + 16 * TL::kRowPitch + 32 * t));
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        const bf16x8 kt = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
+        dq[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt, hi, dq[t], 0, 0, 0);
+        dq[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt, lo, dq[t], 0, 0, 0);
+      }
+      __builtin_amdgcn_wave_barrier();
+      s0 = nx;
+    }
+    bool bad = false;  // a result of the pass is not finite
+    if (!alone) {
+      float sum = 0.0f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) sum += (dq[t][0] + dq[t][1]) + (dq[t][2] + dq[t][3]);
+      bad = __any(!(fabsf(sum) < __builtin_inff())) != 0;
+    }
+    if constexpr (KW == 1) {
+      if (!bad && pr < nr * G) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4*>(a.dQ + rh * D + 16 * t + 4 * quad) = dq[t] * a.scale;
+      }
+    } else {
+      float* so = reinterpret_cast<float*>(sk);
+      if (lane == 0) s_bad[wave] = bad;
+      if (pr < RPW * G) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) *reinterpret_cast<f32x4*>(so + pr * D + 16 * t + 4 * quad) = dq[t];
+      }
+      __syncthreads();
+      bad = false;
+#pragma unroll
+      for (int w = 0; w < KW; ++w) bad |= __builtin_amdgcn_readfirstlane(s_bad[w]) != 0;
+      for (int x = tid; !bad && x < nr * G * (D / 4); x += 64 * KW) {  // the waves' parts in wave order
+        const int p = x / (D / 4), d0 = 4 * (x % (D / 4));
+        f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w = 0; w < KW; ++w) v += *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(s_kv[w]) + p * D + d0);
+        *reinterpret_cast<f32x4*>(a.dQ + ((row0 + p / G) * a.n_q_heads + h * G + p % G) * D + d0) = v * a.scale;
+      }
+      __syncthreads();  // the buffers are read: a further pass may overwrite them
+    }
+    // the next pass: the first row alone, then the one after it, ...
+    if (alone ? row0 + 1 == r_hi || nr == (int)(r_hi - r_lo) : !bad) return;
+    row0 = alone ? row0 + 1 : r_lo;
+    alone = true;
+    nr = 1;
   }
 }
 
@@ -1665,10 +1730,20 @@ template <typename T, int D, int G>
 hipError_t rows_bwd_g(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
   const int64_t q_end = a.q_begin + n_rows;
   const int n_act = (int)((q_end - a.grad_begin + 63) / 64);
-  if constexpr (Elem<T>::kBytes == 2)
-    hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G>), dim3((unsigned)(n_rows * a.n_kv_heads)), dim3(256), 0, s, a);
-  else
+  if constexpr (Elem<T>::kBytes == 2) {
+    constexpr int R = rows_per_group<G>();
+    const int64_t ng = n_row_groups(a, n_rows, R);
+    if (ng * a.n_kv_heads >= kRowsWaveGroups)
+      hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 1>), dim3((unsigned)((ng + 3) / 4 * a.n_kv_heads)), dim3(256),
+                         0, s, a, n_rows, ng);
+    else
+      hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 4>), dim3((unsigned)(ng * a.n_kv_heads)), dim3(256), 0, s, a,
+                         n_rows, ng);
+  } else {
+    const int64_t pairs = n_rows * a.n_q_heads;
+    hipLaunchKernelGGL((rows_rowdot_kernel<T, D>), dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, s, a, n_rows);
     hipLaunchKernelGGL((rows_dq_kernel<T, D, G>), dim3((unsigned)(n_rows * a.n_kv_heads)), dim3(256), 0, s, a);
+  }
   const dim3 dkv_grid((unsigned)(n_act * a.n_kv_heads * (64 / kRowsDkvKeys)));
   if constexpr (Elem<T>::kBytes == 2)
     hipLaunchKernelGGL((rows_dkv_mfma_kernel<D, G>), dkv_grid, dim3(256), 0, s, a, n_rows);
@@ -1679,8 +1754,6 @@ hipError_t rows_bwd_g(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
 
 template <typename T, int D>
 hipError_t rows_bwd_d(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
-  const int64_t pairs = n_rows * a.n_q_heads;
-  hipLaunchKernelGGL((rows_rowdot_kernel<T, D>), dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, s, a, n_rows);
   switch (a.gqa) {
     case 1: return rows_bwd_g<T, D, 1>(a, n_rows, s);
     case 2: return rows_bwd_g<T, D, 2>(a, n_rows, s);

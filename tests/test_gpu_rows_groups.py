@@ -11,7 +11,7 @@ import torch
 
 from paper_2607_15105_amd import hga, synth
 from tests import parity as P
-from tests.test_gpu_rows import _gpu, _rows_check  # noqa: F401
+from tests.test_gpu_rows import _gpu, _rows_bwd_check, _rows_check  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +71,55 @@ def test_rows_not_attending_a_non_finite_value_keep_their_result(n_q, bad):
     assert not torch.isfinite(o2[..., 1][sees_own]).any()
     assert not torch.isfinite(o2[..., 5][sees_sel]).any()
     assert (lse - lse2).abs().max() <= 1e-5
+
+
+# four waves per group of rows below 1,024 (group, kv head) pairs, then one
+@pytest.mark.parametrize("n_q,q_begin", [(3, 1665), (66, 1537), (515, 1501)])
+@pytest.mark.parametrize("G,d", [(1, 64), (2, 64), (4, 128), (8, 64)])
+def test_rows_backward_forms(G, d, n_q, q_begin):
+    wl = synth.Workload("rows_bwd_forms", T=2048, n_q_heads=8 * G, n_kv_heads=8, head_dim=d, dtype="bf16", seed=33,
+                        q_begin=q_begin, n_q=n_q, grad_begin=q_begin // 64 * 64 - 64, key_offset="normal",
+                        top_groups=13, local_tokens=64)
+    _rows_bwd_check(wl, repeat=True)
+
+
+@pytest.mark.parametrize("n_q", [12, 600])
+def test_rows_dq_of_rows_not_attending_a_non_finite_key(n_q):
+    """An infinity in the K row of a token of the call and of a token that
+    some rows select: dQ of the rows that attend neither stays what it is,
+    with D from the bf16 O and from the float32 O."""
+    wl = replace(synth.WORKLOADS["qwen3_8b_2k"], q_begin=1410, n_q=n_q, grad_begin=1408)
+    hc, end = P.hcfg_of(wl), 1410 + n_q
+    K, V = P.to_dev(synth.keys(wl, 0, end)), P.to_dev(synth.values(wl, 0, end))
+    Q, dO = P.to_dev(synth.queries(wl, 1410, end)), P.to_dev(synth.grad_output(wl, 1410, end))
+    cs, gs = hga.alloc_summaries(hc, -(-end // 64) * 64)
+    hga.build_summaries(hc, K, 0, end, cs, gs)
+    sc, sg, ns = hga.alloc_route_rows(hc, n_q)
+    hga.route_rows(hc, Q, 1410, cs, gs, sc, sg, ns)
+    O, lse = torch.empty_like(Q), torch.empty(n_q, wl.n_q_heads, device="cuda")
+    o32 = torch.empty(n_q, wl.n_q_heads, wl.head_dim, device="cuda")
+    hga.attend_rows_fwd(hc, Q, K, V, 1410, sg, ns, O, lse, o32)
+    ws = torch.empty(hga.rows_workspace_size(hc, n_q), dtype=torch.uint8, device="cuda")
+
+    def dq(k, o):
+        out = torch.empty(n_q, wl.n_kv_heads, wl.n_q_heads // wl.n_kv_heads, wl.head_dim, device="cuda")
+        dk = torch.empty(end - 1408, wl.n_kv_heads, wl.head_dim, device="cuda")
+        hga.attend_rows_bwd(hc, Q, k, V, O, dO, lse, 1410, 1408, sg, ns, out, dk, torch.empty_like(dk), ws, o)
+        torch.cuda.synchronize()
+        return out
+
+    g, own, sel = wl.group_size, 1416, int(sg[3, 0, 0])
+    bad = K.clone()
+    bad[own, :, 1] = float("inf")
+    bad[sel * g + 1, 0, 5] = float("inf")
+    rows = torch.arange(n_q, device="cuda")
+    blk = (1410 + rows) // 64 * 64 + 64
+    sees = ((rows >= 6) & (own >= blk - wl.local_tokens))[:, None] | (sg == own // g).any(-1)
+    sees[:, 0] |= (sg[:, 0] == sel).any(-1)
+    clean = ~sees
+    assert clean[:6].any() and sees[:6, 0].any()
+    for o in (o32, None):
+        x, y = dq(K, o), dq(bad, o)
+        assert (x - y)[clean].abs().max() <= 1e-5 * x[clean].abs().max()
+        assert not torch.isfinite(y[sees].sum(-1)).any()
+    assert (dq(K, None) - dq(K, o32)).abs().max() <= 2e-2
