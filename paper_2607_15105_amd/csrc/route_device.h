@@ -183,18 +183,15 @@ __device__ inline int rank_select(TopKScratch& ws, int L, int k_eff, int lane) {
   return nsel;
 }
 
-// Top-k (k <= 64) positions of the scores sc[0..n) (no NaN), returned
-// ascending: lane r < min(k, n) gets the r-th smallest selected position,
-// the other lanes kNoIdx. Called by a whole wave; sc is not modified.
-//
-// When n > 64 the k-th best of the 64 lane bests (each lane's best over its
-// strided slice) is a threshold: the k lane bests at or above it are k
-// entries, so every top-k entry is at or above it too. The entries at or
+// wave_top_k (below) by exact ranks, for inputs whose 32-bit keys tie at the
+// boundary. When n > 64 the k-th best of the 64 lane bests (each lane's best
+// over its strided slice) is a threshold: the k lane bests at or above it are
+// k entries, so every top-k entry is at or above it too. The entries at or
 // above the threshold are compacted in index order (at most k lane slices
 // contribute, so n <= 256 always fits kListCap) and ranked exactly: an
 // entry's rank among them equals its rank among all n.
-__device__ __attribute__((always_inline)) inline int wave_top_k(const double* sc, int n, int k,
-                                                                int lane, TopKScratch& ws) {
+__device__ __attribute__((always_inline)) inline int wave_top_k_ranked(const double* sc, int n, int k,
+                                                                       int lane, TopKScratch& ws) {
   const int k_eff = min(k, n);
   if (k_eff <= 0) return kNoIdx;
   if (k_eff == n) return lane < n ? lane : kNoIdx;  // take all (n <= 64)
@@ -264,91 +261,128 @@ __device__ __attribute__((always_inline)) inline int wave_top_k(const double* sc
   return lane < k_eff && lane < nsel ? ws.out[lane] : kNoIdx;
 }
 
-// wave_top_k for a workgroup that routes a single block: all four waves call
-// it with the same arguments and share the rank comparisons (each compares
-// against a quarter of the entries; wave 0 adds the four partial ranks);
-// wave 0 does the rest. The result lands in wave 0's lanes as wave_top_k's
-// does; the other waves get kNoIdx.
-template <typename Sync>
-__device__ __attribute__((always_inline)) inline int block_top_k(const double* sc, int n, int k, int wave,
-                                                                 int lane, TopKScratch& ws, int (*s_part)[64],
-                                                                 int* s_len, Sync& sync) {
+// Order-preserving 32-bit key of a score: equal scores (-0 and 0 among them)
+// have equal keys, and a larger key means a larger score; scores that round
+// to the same float share a key. 0 is below every score's key.
+__device__ inline uint32_t score_key(double x) {
+  const float f = (float)x + 0.0f;  // -0 to 0
+  const uint32_t u = __float_as_uint(f);
+  return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+
+// The k-th largest key T of the wave's 64 E keys (k >= 1, at least k of them
+// nonzero), bit by bit from the top with a count of the keys at or above; true
+// if exactly k keys are >= T. It stops at the first T that separates them,
+// usually after the exponent and a few bits of the mantissa.
+template <int E>
+__device__ inline bool kth_key(const uint32_t (&key)[E], int k, uint32_t& T) {
+  T = 0;
+#pragma unroll 1
+  for (uint32_t bit = 0x80000000u; bit != 0; bit >>= 1) {
+    const uint32_t c = T | bit;
+    int n = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) n += __popcll(__ballot(key[e] >= c));
+    if (n >= k) T = c;
+    if (n == k) return true;
+  }
+  return false;
+}
+
+// The positions pos[e] of the entries with key[e] >= T, 64 at most, in order
+// of (e, lane), to out; returns how many.
+template <int E>
+__device__ inline void take_keys(const uint32_t (&key)[E], uint32_t T, const int (&pos)[E], int* out) {
+  int base = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const bool q = key[e] >= T;
+    const uint64_t m = __ballot(q);
+    if (q) out[base + lanes_below(m)] = pos[e];
+    base += __popcll(m);
+  }
+}
+
+// Top-k of at most 64 E entries: entry lane + 64 e has score sc[..] and stands
+// for position idx[..] (idx null: itself). False if a tie of keys leaves the
+// set open; else ws.out[0, k) holds the positions in entry order.
+template <int E>
+__device__ inline bool top_k_keys(const double* sc, const int* idx, int n, int k, int lane, TopKScratch& ws) {
+  double v[E];
+  int pos[E];
+  uint32_t key[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) v[e] = sc[min(lane + 64 * e, n - 1)];
+#pragma unroll
+  for (int e = 0; e < E; ++e) pos[e] = idx ? idx[min(lane + 64 * e, n - 1)] : lane + 64 * e;
+#pragma unroll
+  for (int e = 0; e < E; ++e) key[e] = lane + 64 * e < n ? score_key(v[e]) : 0u;
+  uint32_t T;
+  if (!kth_key<E>(key, k, T)) return false;
+  take_keys<E>(key, T, pos, ws.out);
+  __builtin_amdgcn_wave_barrier();
+  return true;
+}
+
+// Top-k (k <= 64) positions of the scores sc[0..n) (no NaN), returned
+// ascending: lane r < min(k, n) gets the r-th smallest selected position,
+// the other lanes kNoIdx. Larger score first, lower position on equal scores.
+// Called by a whole wave; sc is not modified.
+//
+// Only the set is wanted, so nothing is ranked: a threshold with exactly k
+// entries at or above it gives it. Up to 256 entries sit in registers (four a
+// lane) and the threshold is found on their 32-bit keys by ballots. More
+// entries are first cut to those at or above the k-th largest of the 64 lane
+// maxima (k lane maxima reach it, so every top-k entry does). Where keys tie
+// at the boundary the exact ranking decides. (One decode step at 131K: 16 of
+// 2,027 chunk scores and 32 of 128 group scores took 15.2 + 8.7 and 9.8 thousand
+// cycles with ranks counted in LDS, 7.5 + 4 and 3.7 so. Two bits of the key per
+// step were no faster.)
+__device__ __attribute__((always_inline)) inline int wave_top_k(const double* sc, int n, int k, int lane,
+                                                                TopKScratch& ws) {
   const int k_eff = min(k, n);
   if (k_eff <= 0) return kNoIdx;
-  if (k_eff == n) return wave == 0 && lane < n ? lane : kNoIdx;  // take all (n <= 64)
+  if (k_eff == n) return lane < n ? lane : kNoIdx;  // take all (n <= 64)
+  bool done = false;
   if (n <= 64) {
-    if (wave == 0) {
-      ws.lv[lane] = lane < n ? sc[lane] : -__builtin_inf();
-      ws.li[lane] = lane < n ? lane : kNoIdx;
-    }
+    done = top_k_keys<1>(sc, nullptr, n, k_eff, lane, ws);
+  } else if (n <= 256) {
+    done = top_k_keys<4>(sc, nullptr, n, k_eff, lane, ws);
   } else {
-    // threshold: the k-th best of the 64 lane bests (see wave_top_k)
-    double bv = -__builtin_inf();
-    int bi = kNoIdx;
-    if (wave == 0) {
-      for (int i0 = lane; i0 < n; i0 += 256) {
-        double v[4];
+    uint32_t best[1] = {0};
+    for (int i0 = lane; i0 < n; i0 += 256) {
+      double v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = sc[min(i0 + 64 * u, n - 1)];
+      for (int u = 0; u < 4; ++u) v[u] = sc[min(i0 + 64 * u, n - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int p = i0 + 64 * u;
-          const bool b = (p < n) & better_nb(v[u], p, bv, bi);
-          bv = b ? v[u] : bv;
-          bi = b ? p : bi;
+      for (int u = 0; u < 4; ++u) best[0] = max(best[0], i0 + 64 * u < n ? score_key(v[u]) : 0u);
+    }
+    uint32_t T;
+    kth_key<1>(best, k_eff, T);
+    int L = 0;
+    for (int j0 = 0; j0 < n; j0 += 256) {
+      double v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = sc[min(j0 + 64 * u + lane, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int p = j0 + 64 * u + lane;
+        const bool q = (p < n) & (score_key(v[u]) >= T);
+        const uint64_t m = __ballot(q);
+        const int pos = L + lanes_below(m);
+        if (q && pos < kListCap) {
+          ws.lv[pos] = v[u];
+          ws.li[pos] = p;
         }
+        L += __popcll(m);
       }
-      ws.lbv[lane] = bv;
-      ws.lbi[lane] = bi;
     }
-    sync();
-    s_part[wave][lane] = rank_among(ws.lbv + 16 * wave, ws.lbi + 16 * wave, 16, ws.lbv[lane], ws.lbi[lane]);
-    sync();
-    if (wave == 0) {
-      const int rk = s_part[0][lane] + s_part[1][lane] + s_part[2][lane] + s_part[3][lane];
-      const uint64_t mt = __ballot(rk == k_eff - 1);
-      const int tl = __builtin_ctzll(mt);
-      const double tv = readlane_d(bv, tl);
-      const int ti = __builtin_amdgcn_readlane(bi, tl);
-      int base = 0;
-      for (int j0 = 0; j0 < n; j0 += 256) {
-        double v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = sc[min(j0 + 64 * u + lane, n - 1)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int p = j0 + 64 * u + lane;
-          const bool q = (p < n) & ((p == ti) | better_nb(v[u], p, tv, ti));
-          const uint64_t mq = __ballot(q);
-          const int pos = base + lanes_below(mq);
-          if (q && pos < kListCap) { ws.lv[pos] = v[u]; ws.li[pos] = p; }
-          base += __popcll(mq);
-        }
-      }
-      if (lane == 0) *s_len = base;
-    }
+    __builtin_amdgcn_wave_barrier();
+    if (L <= 64) done = top_k_keys<1>(ws.lv, ws.li, L, k_eff, lane, ws);
+    else if (L <= kListCap) done = top_k_keys<4>(ws.lv, ws.li, L, k_eff, lane, ws);
   }
-  sync();  // the list to rank
-  const int L = n <= 64 ? n : *s_len;
-  if (L > kListCap) return wave == 0 ? top_k_tournament(sc, n, k_eff, lane) : kNoIdx;
-  int nsel = 0;
-  if (L <= 64) {
-    const int lo = 16 * wave, cnt = max(0, min(16, L - lo));
-    s_part[wave][lane] = rank_among(ws.lv + lo, ws.li + lo, cnt, ws.lv[lane], ws.li[lane]);
-    sync();
-    if (wave == 0) {
-      const int rk = s_part[0][lane] + s_part[1][lane] + s_part[2][lane] + s_part[3][lane];
-      const bool sel = (lane < L) & (rk < k_eff);
-      const uint64_t ms = __ballot(sel);
-      if (sel) ws.out[lanes_below(ms)] = ws.li[lane];
-      nsel = __popcll(ms);
-    }
-  } else if (wave == 0) {
-    nsel = L <= 128 ? rank_select<2>(ws, L, k_eff, lane) : rank_select<kListCap / 64>(ws, L, k_eff, lane);
-  }
-  if (wave != 0) return kNoIdx;
-  __builtin_amdgcn_wave_barrier();
-  return lane < k_eff && lane < nsel ? ws.out[lane] : kNoIdx;
+  if (!done) return wave_top_k_ranked(sc, n, k, lane, ws);
+  return lane < k_eff ? ws.out[lane] : kNoIdx;
 }
 
 // One past the last candidate chunk of absolute query block `blk`: chunks end
@@ -425,11 +459,9 @@ __device__ __forceinline__ void route_blocks(const RouteArgs& a, int wg, bool wr
   __shared__ TopKScratch s_tk[TB];
   __shared__ double s_kv[TB][64];  // rounds: each block's running selection (scores, chunk ids)
   __shared__ int s_ki[TB][64];
-  __shared__ int s_part[4][64];  // one block per workgroup: partial ranks of the four waves
   // rounds: the round's candidates that beat a block's running k-th best
   __shared__ double s_sv[TB > 1 ? TB : 1][64];
   __shared__ int s_sf[TB > 1 ? TB : 1][64];
-  __shared__ int s_len;
 
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -698,7 +730,7 @@ __device__ __forceinline__ void route_blocks(const RouteArgs& a, int wg, bool wr
     const int kc_eff = min(a.top_chunks, n_cand);
     int chunk = kNoIdx;
     if constexpr (TB == 1) {
-      const int pos = block_top_k(dyn, n_cand, a.top_chunks, wave, lane, s_tk[0], s_part, &s_len, sync);
+      const int pos = wave == 0 ? wave_top_k(dyn, n_cand, a.top_chunks, lane, s_tk[0]) : kNoIdx;
       chunk = pos == kNoIdx ? kNoIdx : c_lo + pos;
     } else if (wave < nb) {
       chunk = lane < n_kept ? s_ki[t][lane] : kNoIdx;
@@ -823,8 +855,7 @@ __device__ __forceinline__ void route_blocks(const RouteArgs& a, int wg, bool wr
     const int kg_eff = min(a.top_groups, n_gc);
     int pos = kNoIdx;
     if (a.top_groups > 0) {
-      if constexpr (TB == 1) pos = block_top_k(dyn, n_gc, a.top_groups, wave, lane, s_tk[0], s_part, &s_len, sync);
-      else if (wave < nb) pos = wave_top_k(dyn + wave * stride, n_gc, a.top_groups, lane, s_tk[wave]);
+      if (wave < nb) pos = wave_top_k(dyn + wave * stride, n_gc, a.top_groups, lane, s_tk[wave]);
     }
     if (wave < nb && a.top_groups > 0) {
       if (lane < a.top_groups) {

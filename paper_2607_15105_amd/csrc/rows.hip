@@ -63,30 +63,24 @@ __device__ inline double summary_dot(const float* table, int64_t r, int64_t cap,
 
 // Float64 dots of summary row r with the descriptors q[0..nv): per
 // descriptor the two FMA chains of summary_dot, in the same order, with the
-// row read and converted once for all of them.
+// row read and converted once for all of them. Sixteen elements at a time in
+// two load slots, so that the kernel keeps four waves per SIMD.
 template <int D, int RB>
 __device__ inline void summary_dots(const float* table, int64_t r, int64_t cap, const double (*q)[D], int nv,
                                     double (&out)[RB]) {
-  const f32x4* t = reinterpret_cast<const f32x4*>(table) + r;
-  f32x4 v[D / 4];
-#pragma unroll
-  for (int k = 0; k < D / 4; ++k) v[k] = t[(int64_t)k * cap];  // every load in flight
+  constexpr int U = D / 16;  // units of a row
+  f32x4 va[4], vb[4];
   double a0[RB], a1[RB];
 #pragma unroll
   for (int w = 0; w < RB; ++w) a0[w] = a1[w] = 0.0;
+  load_unit<D, U>(va, table, r, cap, 0);
+  load_unit<D, U>(vb, table, r, cap, 1);
 #pragma unroll
-  for (int k = 0; k < D / 4; ++k) {
-    const double x0 = v[k][0], x1 = v[k][1], x2 = v[k][2], x3 = v[k][3];
-#pragma unroll
-    for (int w = 0; w < RB; ++w) {
-      if (w < nv) {
-        a0[w] = fma(x0, q[w][4 * k], a0[w]);
-        a1[w] = fma(x1, q[w][4 * k + 1], a1[w]);
-        a0[w] = fma(x2, q[w][4 * k + 2], a0[w]);
-        a1[w] = fma(x3, q[w][4 * k + 3], a1[w]);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
+  for (int u = 0; u < U; u += 2) {
+    unit_dots<D, U, RB>(va, q, u, nv, a0, a1);
+    if (u + 2 < U) load_unit<D, U>(va, table, r, cap, u + 2);
+    unit_dots<D, U, RB>(vb, q, u + 1, nv, a0, a1);
+    if (u + 3 < U) load_unit<D, U>(vb, table, r, cap, u + 3);
   }
 #pragma unroll
   for (int w = 0; w < RB; ++w) out[w] = a0[w] + a1[w];
@@ -107,8 +101,16 @@ struct RowsRoute {
   static constexpr int RR = RB == 1 ? kRowsRouteRound : 512;
 };
 
-template <typename T, int D, int RB>
-__global__ __launch_bounds__(256) void route_rows_kernel(RouteArgs a, int64_t n_rows, int stride) {
+// NT threads: 256, or 1,024 for one row with more than 256 candidates. There
+// the sixteen waves score 1,024 candidates a pass and each selects from a
+// sixteenth of the round (contiguous, so that kept positions stay in chunk
+// order); wave 0 then selects from the kept entries of all. (Decode step at
+// 131K, 2,027 candidates: 34 us with four waves and one selection by ranks,
+// 23 us so. The scoring takes half of it: the CU's float64 conversions and the
+// descriptor's LDS reads, not the summary rows; four load slots were no faster.)
+template <typename T, int D, int RB, int NT>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(RB == 1 && NT == 256 ? 1 : 4))) void
+route_rows_kernel(RouteArgs a, int64_t n_rows, int stride) {
   constexpr int EB = Elem<T>::kBytes;
   constexpr int RR = RowsRoute<RB>::RR;
   static_assert(RB <= 4, "one selecting wave per row");
@@ -118,6 +120,10 @@ __global__ __launch_bounds__(256) void route_rows_kernel(RouteArgs a, int64_t n_
   __shared__ double s_kv[RB][64];
   __shared__ int s_ki[RB][64];
   __shared__ int s_chunks[RB][64];
+  constexpr int NWS = NT / 64;  // waves that share a selection (RB == 1, NT > 256)
+  __shared__ double s_cv[NT > 256 ? NWS * 64 : 1];  // their kept entries, compacted
+  __shared__ int s_ci[NT > 256 ? NWS * 64 : 1];
+  __shared__ TopKScratch s_tkw[NT > 256 ? NWS : 1];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = blockIdx.x % a.n_kv_heads;
@@ -127,7 +133,7 @@ __global__ __launch_bounds__(256) void route_rows_kernel(RouteArgs a, int64_t n_
 
   // descriptors: the mean of each row's G head rows of kv head h (a sum of G
   // bf16 or float32 values and a division by a power of two: exact)
-  for (int x = tid; x < RB * D; x += 256) {
+  for (int x = tid; x < RB * D; x += NT) {
     const int w = x / D, e = x % D;
     double s = 0.0;
     if (w < nv) {
@@ -154,10 +160,11 @@ __global__ __launch_bounds__(256) void route_rows_kernel(RouteArgs a, int64_t n_
   for (int r = 0; r < n_rounds; ++r) {
     const int nr = max(0, min(RR, n_max - r * RR));
     const int r0 = c_lo + r * RR;
-    for (int i0 = 0; i0 < nr; i0 += 256) {
+    for (int i0 = 0; i0 < nr; i0 += NT) {
       const int i = i0 + tid;
       double v[RB];
-      summary_dots<D, RB>(cs, r0 + min(i, nr - 1), a.chunk_cap, s_q, nv, v);
+      if constexpr (RB == 1 && NT == 256) v[0] = summary_dot<D>(cs, r0 + min(i, nr - 1), a.chunk_cap, s_q[0]);
+      else summary_dots<D, RB>(cs, r0 + min(i, nr - 1), a.chunk_cap, s_q, nv, v);
       if (i < nr) {
 #pragma unroll
         for (int w = 0; w < RB; ++w)
@@ -165,7 +172,25 @@ __global__ __launch_bounds__(256) void route_rows_kernel(RouteArgs a, int64_t n_
       }
     }
     __syncthreads();
-    const int nr_w = max(0, min(RR, my_n - r * RR));
+    int nr_w = max(0, min(RR, my_n - r * RR));
+    bool listed = false;
+    if constexpr (NT > 256) {
+      // every wave its slice; the kept entries of all replace the round's
+      const int per = (nr + NWS - 1) / NWS, lo = min(wave * per, nr), cnt = min(per, nr - lo);
+      const int ke = min(a.top_chunks, per);  // entries a full slice keeps
+      listed = ke * NWS < nr;
+      if (listed) {
+        const int p = wave_top_k(dyn + 64 + lo, cnt, ke, lane, s_tkw[wave]);
+        if (lane < ke) {
+          s_cv[wave * ke + lane] = lane < cnt ? dyn[64 + lo + p] : -__builtin_inf();
+          s_ci[wave * ke + lane] = lane < cnt ? r0 + lo + p : kNoIdx;
+        }
+        __syncthreads();
+        nr_w = nr / per * ke + min(ke, nr % per);  // full slices, then at most one short one
+        for (int i = tid; i < NWS * ke; i += NT) dyn[64 + i] = s_cv[i];
+        __syncthreads();
+      }
+    }
     if (wave < nv && nr_w > 0) {
       double* base = mine + 64 - n_kept;
       if (lane < n_kept) base[lane] = s_kv[wave][lane];
@@ -177,7 +202,7 @@ __global__ __launch_bounds__(256) void route_rows_kernel(RouteArgs a, int64_t n_
       int idx = -1;
       if (lane < k_eff) {  // pc is a position only on those lanes
         v = base[pc];
-        idx = pc < n_kept ? s_ki[wave][pc] : r0 + (pc - n_kept);
+        idx = pc < n_kept ? s_ki[wave][pc] : NT > 256 && listed ? s_ci[pc - n_kept] : r0 + (pc - n_kept);
       }
       __builtin_amdgcn_wave_barrier();
       if (lane < k_eff) {
@@ -204,11 +229,17 @@ __global__ __launch_bounds__(256) void route_rows_kernel(RouteArgs a, int64_t n_
   const int gslot = a.top_chunks << gpc_shift;  // items per row
   if (a.top_groups > 0 && gslot > 0) {
     const float* gs = a.group_sum + quad_off(h, 0, 0, D, a.group_cap);
-    for (int f0 = 0; f0 < nv * gslot; f0 += 256) {
+    for (int f0 = 0; f0 < nv * gslot; f0 += NT) {
       const int fa = f0 + tid, w = fa / gslot, f = fa - w * gslot;
       if (w < nv && f < (min(a.top_chunks, n_cand_of(w)) << gpc_shift)) {
         const int64_t j = ((int64_t)s_chunks[w][f >> gpc_shift] << gpc_shift) + (f & gmask);
-        dyn[w * stride + f] = no_nan(summary_dot<D>(gs, j, a.group_cap, s_q[w]));
+        if constexpr (RB == 1 && NT == 256) {
+          dyn[w * stride + f] = no_nan(summary_dot<D>(gs, j, a.group_cap, s_q[w]));
+        } else {
+          double v[1];
+          summary_dots<D, 1>(gs, j, a.group_cap, s_q + w, 1, v);
+          dyn[w * stride + f] = no_nan(v[0]);
+        }
       }
     }
   }
@@ -241,16 +272,21 @@ hipError_t launch_route_rows(const RouteArgs& a, int64_t n_rows, int n_cand_max,
   const int nc = 64 + (n_cand_max < rr ? n_cand_max : rr);
   const int stride = nc > group_cand ? nc : group_cand;
   const size_t lds = (size_t)rb * stride * sizeof(double);
-  const dim3 grid((unsigned)((n_rows + rb - 1) / rb * a.n_kv_heads)), block(256);
-#define HGA_RR(T, D, RB) hipLaunchKernelGGL((route_rows_kernel<T, D, RB>), grid, block, lds, s, a, n_rows, stride)
-  if (rb == 1) {
-    if (!bf16) HGA_RR(float, 64, 1);
-    else if (head_dim == 64) HGA_RR(__bf16, 64, 1);
-    else HGA_RR(__bf16, 128, 1);
+  const dim3 grid((unsigned)((n_rows + rb - 1) / rb * a.n_kv_heads));
+#define HGA_RR(T, D, RB, NT) \
+  hipLaunchKernelGGL((route_rows_kernel<T, D, RB, NT>), grid, dim3(NT), lds, s, a, n_rows, stride)
+  if (rb == 1 && n_cand_max > 256) {
+    if (!bf16) HGA_RR(float, 64, 1, 1024);
+    else if (head_dim == 64) HGA_RR(__bf16, 64, 1, 1024);
+    else HGA_RR(__bf16, 128, 1, 1024);
+  } else if (rb == 1) {
+    if (!bf16) HGA_RR(float, 64, 1, 256);
+    else if (head_dim == 64) HGA_RR(__bf16, 64, 1, 256);
+    else HGA_RR(__bf16, 128, 1, 256);
   } else {
-    if (!bf16) HGA_RR(float, 64, 4);
-    else if (head_dim == 64) HGA_RR(__bf16, 64, 4);
-    else HGA_RR(__bf16, 128, 4);
+    if (!bf16) HGA_RR(float, 64, 4, 256);
+    else if (head_dim == 64) HGA_RR(__bf16, 64, 4, 256);
+    else HGA_RR(__bf16, 128, 4, 256);
   }
 #undef HGA_RR
   return hipGetLastError();
