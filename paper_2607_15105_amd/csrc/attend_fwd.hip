@@ -28,9 +28,9 @@ namespace hga {
 // Window tiles (sink and local, known without the routing) come first and
 // their gathers go out with the query rows. The selected groups follow:
 //  - LATE == false: `routed(rs)` completes rs from the routing row once the
-//    window gathers are out; `sync` then makes its LDS writes visible. Three
-//    register slots rotate, so tiles t+1..t+3 are in flight while tile t is
-//    computed.
+//    window gathers are out; `sync` then makes its LDS writes visible. Two
+//    register slots alternate: while tile t is computed, tile t+1 waits in
+//    one and tile t+2 is in flight in the other.
 //  - LATE == true: the routing is computed by other waves of the workgroup
 //    while these attend the window tiles. `ready()` polls whether it has
 //    landed (each wave on its own); the gathers of selected groups go out as
@@ -125,8 +125,7 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
   // two 32-key halves, each an online-softmax step of its own: the second
   // half's S products and the first half's P.V products overlap the other
   // half's max and exponentials.
-  auto compute = [&](int tile) {
-    const char* st = smem + (tile & 1) * STAGE;
+  auto compute = [&](int tile, const char* st) __attribute__((always_inline)) {
     // S^T = K . Q^T : two 32-key tiles, raw scores
     f32x16 sacc[2] = {f32x16{}, f32x16{}};
 #pragma unroll
@@ -140,19 +139,21 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
     // the same for every lane of the wave; read as a scalar so the masked
     // path is a branch, not a select over every tile
     const bool need_mask = __builtin_amdgcn_readfirstlane((int)rs.tile_needs_mask(tile * 64, (wave & 1) * 32)) != 0;
+    if (need_mask) {  // both halves under one branch: under two, the second became selects in every tile
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      if (need_mask) {
+      for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int p = tile * 64 + 32 * t + 8 * (v >> 2) + 4 * hh + (v & 3);
           if (rs.masked(p, qoff)) sacc[t][v] = -__builtin_inff();
         }
-      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
       float mx = -__builtin_inff();
 #pragma unroll
       for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[t][v]);
-      mx = fmaxf(mx, xor32(mx));
+      mx = half_max(mx);
       const bool raise = mx > m_run + lazy;  // also true on the first half-tile (m_run = -inf)
       if (__any(raise)) {
         const float m_new = raise ? mx : m_run;
@@ -172,7 +173,7 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
       }
       l_run += psum;
       // O^T += V^T . P^T over this half's keys
-#pragma unroll
+  #pragma unroll
       for (int s2 = 0; s2 < VPS; ++s2) {
         const int s = t * VPS + s2;
         float pv[E], plo[E];
@@ -191,42 +192,48 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
           if constexpr (PREC) oacc[dt] = EL::mma(vf, EL::frag_from(plo), oacc[dt]);
         }
       }
-    }
+      }
   };
 
   if constexpr (!LATE) {
-    KV kv0, kv1, kv2;
+    // Tile x lives in kv0 for even x, kv1 for odd x; its LDS stage is x & 1.
+    KV kv0, kv1;
     gather_w(kv0, 0);  // always a window tile
     if (nwt > 1) gather_w(kv1, 1);
-    if (nwt > 2) gather_w(kv2, 2);
     take_routing();
     sync();  // the routing row's LDS copy
-    const int ntiles = ntl;
-    if (nwt <= 1 && ntiles > 1) gather(kv1, 1);
-    if (nwt <= 2 && ntiles > 2) gather(kv2, 2);
+    const int last = ntl - 1;
+    if (nwt <= 1) gather(kv1, min(1, last));
     put(kv0, smem);
-    if (ntiles > 3) gather(kv0, 3);
+    gather(kv0, min(2, last));
     settle(qf);
     sync();
-    for (int tile = 0; tile < ntiles; ++tile) {
-      compute(tile);
-      // the slot holding tile+1 goes to LDS, then refills with tile+4
-      if (tile + 1 < ntiles) {
-        char* nx = smem + ((tile + 1) & 1) * STAGE;
-        const int j = tile % 3;
-        if (j == 0) {
-          put(kv1, nx);
-          if (tile + 4 < ntiles) gather(kv1, tile + 4);
-        } else if (j == 1) {
-          put(kv2, nx);
-          if (tile + 4 < ntiles) gather(kv2, tile + 4);
-        } else {
-          put(kv0, nx);
-          if (tile + 4 < ntiles) gather(kv0, tile + 4);
-        }
-      }
+    // Two tiles per round, so that each slot and stage is named statically. A
+    // slot chosen at run time (three of them, before) made the compiler load
+    // into the free S registers, wait, and copy: every tile then waited for
+    // the gather that it had just sent. Refills are unconditional, on tile
+    // indices clamped to the last (loaded again and not used).
+    // The loop leaves no round half done: an exit between the refills would
+    // make every store wait for both slots.
+    int tile = 0;
+#pragma unroll 1
+    for (; tile + 2 <= last; tile += 2) {
+      compute(tile, smem);
+      put(kv1, smem + STAGE);
+      gather(kv1, min(tile + 3, last));
+      sync();
+      compute(tile + 1, smem + STAGE);
+      put(kv0, smem);
+      gather(kv0, min(tile + 4, last));
       sync();
     }
+    compute(tile, smem);
+    if (tile < last) {
+      put(kv1, smem + STAGE);
+      sync();
+      compute(tile + 1, smem + STAGE);
+    }
+    sync();  // the last tile's stage is no longer read
   } else {
     // Slots A, B: tile x lives in kv0 for even x, kv1 for odd x. nl is the
     // next tile to gather; a selected-group tile whose routing this wave has
@@ -249,7 +256,7 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
     // iteration t: compute tile t; tile t+1 (slot A) to LDS; gathers of
     // t+2 (slot B, free since tile t went to LDS) and t+3 (slot A)
     auto iter = [&](int t, KV& A, KV& B) -> bool {
-      compute(t);
+      compute(t, smem + (t & 1) * STAGE);
       if (t + 1 >= ntl) {
         if (have) return false;
         while (!ready()) __builtin_amdgcn_s_sleep(2);
@@ -271,75 +278,83 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
 
   // Epilogue: O = O^T / l, LSE = (m + log2 l) * ln 2. A lane holds half the
   // head dim of one query row, so storing from registers would scatter every
-  // store instruction over 32 rows; the rows go through LDS instead (the
-  // stages are free now), HR query heads at a time, and leave as 16-byte
-  // pieces with consecutive lanes on consecutive pieces of a row.
+  // store instruction over 32 rows; each wave's 32 rows go through its share
+  // of LDS instead (the stages are free now), as output elements, and leave
+  // as 16-byte pieces with consecutive lanes on consecutive pieces of a row.
+  // No barrier: a wave reads only its own rows.
   if constexpr (LATE) sync();  // the last tile's stage is no longer read
-  const float l = l_run + xor32(l_run);
+  const float l = half_sum(l_run);
   const float inv = 1.0f / l;
   if (hh == 0) a.lse[(int64_t)row * a.n_q_heads + hq] = (m_run * c + __log2f(l)) * kLn2;
-  constexpr int OP = D + 4;  // float pitch of a staged row
-  constexpr int HR = (2 * STAGE) / (64 * OP * 4) >= GW ? GW : 2;
-  static_assert(HR * 64 * OP * 4 <= 2 * STAGE, "staged output rows fit the stages");
-  constexpr int NT = 128 * GW;
-  float* ost = reinterpret_cast<float*>(smem);
-  const int hq0 = wc.h * a.gqa + wc.hs * GW;
+  constexpr int OP = EB == 2 ? D * 2 + 16 : D * 4;  // byte pitch of a staged row
+  constexpr int WB = 2 * STAGE / (2 * GW) / 16 * 16;  // a wave's share
+  static_assert(32 * OP <= WB, "a wave's rows fit its share");
+  char* ost = smem + wave * WB;
+  const int64_t row0 = (int64_t)wc.b * 64 + (wave & 1) * 32;  // the wave's first row
+  // the wave's staged rows to rows `stride` bytes apart
+  auto drain = [&](char* dst, int64_t stride) __attribute__((always_inline)) {
+    constexpr int CPR = (EB == 2 ? D * 2 : D * 4) / 16;
 #pragma unroll
-  for (int r0 = 0; r0 < GW; r0 += HR) {
-    if ((wave >> 1) >= r0 && (wave >> 1) < r0 + HR) {
-      float* dst = ost + (((wave >> 1) - r0) * 64 + qoff) * OP;
-#pragma unroll
-      for (int dt = 0; dt < NDT; ++dt)
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4)
-          *reinterpret_cast<f32x4*>(dst + 32 * dt + 8 * v4 + 4 * hh) =
-              f32x4{oacc[dt][4 * v4] * inv, oacc[dt][4 * v4 + 1] * inv, oacc[dt][4 * v4 + 2] * inv,
-                    oacc[dt][4 * v4 + 3] * inv};
+    for (int it = 0; it < 32 * CPR / 64; ++it) {
+      const int cc = (lane + 64 * it) % CPR, r = (lane + 64 * it) / CPR;
+      *reinterpret_cast<u32x4*>(dst + r * stride + cc * 16) = *reinterpret_cast<const u32x4*>(ost + r * OP + cc * 16);
     }
-    sync();
-    // item = (row r, head j, piece c), head fastest after the piece: with
-    // adjacent query heads a row's HR heads are one contiguous run
-    {
-      constexpr int EPP = 16 / EB;  // elements per 16-byte piece
-      constexpr int CPR = D / EPP;
+  };
+  auto scaled = [&](int dt, int v4) __attribute__((always_inline)) {
+    return f32x4{oacc[dt][4 * v4] * inv, oacc[dt][4 * v4 + 1] * inv, oacc[dt][4 * v4 + 2] * inv,
+                 oacc[dt][4 * v4 + 3] * inv};
+  };
 #pragma unroll
-      for (int it = 0; it < 64 * HR * CPR / NT; ++it) {
-        const int item = tid + it * NT;
-        const int cc = item % CPR, rj = item / CPR, j = rj % HR, r = rj / HR;
-        const float* src = ost + (j * 64 + r) * OP + cc * EPP;
-        char* dst = static_cast<char*>(a.Out) +
-                    (((int64_t)wc.b * 64 + r) * a.out_tok + (int64_t)(hq0 + r0 + j) * a.out_head) * EB + cc * 16;
-        if constexpr (EB == 2) {
-          const f32x4 x0 = *reinterpret_cast<const f32x4*>(src), x1 = *reinterpret_cast<const f32x4*>(src + 4);
-          uint4 w;
-          w.x = float_to_bf16_bits(x0[0]) | (float_to_bf16_bits(x0[1]) << 16);
-          w.y = float_to_bf16_bits(x0[2]) | (float_to_bf16_bits(x0[3]) << 16);
-          w.z = float_to_bf16_bits(x1[0]) | (float_to_bf16_bits(x1[1]) << 16);
-          w.w = float_to_bf16_bits(x1[2]) | (float_to_bf16_bits(x1[3]) << 16);
-          *reinterpret_cast<uint4*>(dst) = w;
-        } else {
-          *reinterpret_cast<f32x4*>(dst) = *reinterpret_cast<const f32x4*>(src);
-        }
+  for (int dt = 0; dt < NDT; ++dt)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+      const f32x4 x = scaled(dt, v4);
+      char* dst = ost + l32 * OP + (32 * dt + 8 * v4 + 4 * hh) * EB;
+      if constexpr (EB == 2)
+        *reinterpret_cast<uint2*>(dst) = uint2{float_to_bf16_bits(x[0]) | (float_to_bf16_bits(x[1]) << 16),
+                                               float_to_bf16_bits(x[2]) | (float_to_bf16_bits(x[3]) << 16)};
+      else
+        *reinterpret_cast<f32x4*>(dst) = x;
+    }
+  __builtin_amdgcn_wave_barrier();
+  drain(static_cast<char*>(a.Out) + (row0 * a.out_tok + (int64_t)hq * a.out_head) * EB, a.out_tok * EB);
+  if (a.o32) {
+    char* dst = reinterpret_cast<char*>(a.o32 + (row0 * a.n_q_heads + hq) * D);
+    const int64_t stride = (int64_t)a.n_q_heads * D * 4;
+    if constexpr (EB == 2) {  // float32 rows are twice as long: half the head dim at a time
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int dt = 0; dt < NDT / 2; ++dt)
+#pragma unroll
+          for (int v4 = 0; v4 < 4; ++v4)
+            *reinterpret_cast<f32x4*>(ost + l32 * OP + (32 * dt + 8 * v4 + 4 * hh) * 4) = scaled(p * (NDT / 2) + dt, v4);
+        __builtin_amdgcn_wave_barrier();
+        drain(dst + p * D * 2, stride);
       }
+    } else {
+      drain(dst, stride);
     }
-    if (a.o32) {
-      constexpr int CPR = D / 4;
-#pragma unroll
-      for (int it = 0; it < 64 * HR * CPR / NT; ++it) {
-        const int item = tid + it * NT;
-        const int cc = item % CPR, rj = item / CPR, j = rj % HR, r = rj / HR;
-        *reinterpret_cast<f32x4*>(a.o32 + (((int64_t)wc.b * 64 + r) * a.n_q_heads + hq0 + r0 + j) * D + 4 * cc) =
-            *reinterpret_cast<const f32x4*>(ost + (j * 64 + r) * OP + 4 * cc);
-      }
-    }
-    if (r0 + HR < GW) sync();  // the next heads' rows overwrite these
   }
 }
 
+// bf16 with head dim 64, two heads: 37 KB of LDS and few enough registers for
+// three workgroups per CU.
+template <typename T, int D, int GW>
+constexpr bool three_per_simd() { return Elem<T>::kBytes == 2 && D == 64 && GW == 2; }
+
 // CMP: over the compact copies of hga_gather_routed (only the routing counts
 // are read; the rows come in tile order).
+//
+// What bounds it: at d = 128 a CU holds one workgroup (two waves per SIMD), and
+// a tile's LDS reads, matrix products and exponentials take about as long
+// each; they overlap only as far as the two waves are apart. 131,072 queries,
+// Qwen3-8B layer, 576 routed keys: 1,938 us when every tile waited for its own
+// gather and the softmax maximum went through the LDS crossbar, 1,590 us (737
+// TFLOP/s) now.
 template <typename T, int D, int GW, bool PREC, bool CMP>
-__global__ __launch_bounds__(128 * GW) void attend_fwd_kernel(AttnArgs a) {
+__global__ __launch_bounds__(128 * GW) __attribute__((amdgpu_waves_per_eu(three_per_simd<T, D, GW>() ? 3 : 1))) void attend_fwd_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[2 * (Tile<T, D>::kRowBytes +
                                                          (Elem<T>::kBytes == 2 ? Tile<T, D>::kRowBytes
                                                                                : Tile<T, D>::kTBytes))];
@@ -403,13 +418,18 @@ template <typename T, int D, bool PREC, bool CMP = false>
 static hipError_t fwd_dispatch(const AttnArgs& a, hipStream_t s) {
   // four query heads per workgroup share each gathered tile; with fewer
   // (block, kv head) pairs than the chip has CUs, two heads per workgroup
-  // fill it instead
+  // fill it instead. bf16 with d = 64 takes two heads always: three such
+  // workgroups fit a CU and hide each other's start and end (10,048 queries,
+  // G = 8: 50 us against 60 with four heads and one workgroup per CU; at
+  // d = 128, where two fit, 131,072 queries take 1,759 against 1,590).
   int gw = a.gqa >= 4 ? 4 : a.gqa;
+  if (gw == 4 && three_per_simd<T, D, 2>()) gw = 2;
   if (gw == 4 && (int64_t)a.n_qb * a.n_kv_heads * (a.gqa / 4) < 256) gw = 2;
   const dim3 grid(a.n_qb * a.n_kv_heads * (a.gqa / gw));
-  if (gw == 4)
-    hipLaunchKernelGGL((attend_fwd_kernel<T, D, 4, PREC, CMP>), grid, dim3(512), 0, s, a);
-  else if (gw == 2)
+  if (gw == 4) {
+    if constexpr (!three_per_simd<T, D, 2>())
+      hipLaunchKernelGGL((attend_fwd_kernel<T, D, 4, PREC, CMP>), grid, dim3(512), 0, s, a);
+  } else if (gw == 2)
     hipLaunchKernelGGL((attend_fwd_kernel<T, D, 2, PREC, CMP>), grid, dim3(256), 0, s, a);
   else
     hipLaunchKernelGGL((attend_fwd_kernel<T, D, 1, PREC, CMP>), grid, dim3(128), 0, s, a);

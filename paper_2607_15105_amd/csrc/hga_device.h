@@ -147,8 +147,26 @@ __device__ inline bf16x8 tr_frag(const char* tile, int col_base, int ra, int rb,
   return __builtin_bit_cast(bf16x8, both);
 }
 
-// Wave-wide helpers.
-__device__ inline float xor32(float x) { return __shfl_xor(x, 32, 64); }
+// Swaps the odd 16-lane rows of x with the even rows of y (or the upper half
+// of x with the lower half of y): with y a copy of x the two then hold, in
+// every lane, its own value and that of lane ^ 16 (^ 32), in some order. (As
+// asm with two operands of its own: the builtin with one value for both
+// gives one register for both results. The wait states are the ones that a
+// lane swap needs after a vector write.)
+__device__ inline void swap16(float& x, float& y) { asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y)); }
+__device__ inline void swap32(float& x, float& y) { asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y)); }
+
+// Maximum and sum over the lanes l and l ^ 32, the same in both.
+__device__ inline float half_max(float x) {
+  float y = x;
+  swap32(x, y);
+  return fmaxf(x, y);
+}
+__device__ inline float half_sum(float x) {
+  float y = x;
+  swap32(x, y);
+  return x + y;
+}
 
 // Barrier of the whole workgroup.
 struct WgSync {

@@ -538,15 +538,6 @@ constexpr int kRowsStep = 32;  // keys of a step
 // and 8.2 with twelve per row, 64 rows 12.7 and 14.7.
 constexpr int64_t kRowsWaveGroups = 1024, kRowsSplitPairs = 512;
 
-// Swaps the odd 16-lane rows of x with the even rows of y (or the upper half
-// of x with the lower half of y): with y a copy of x the two then hold, in
-// every lane, its own value and that of lane ^ 16 (^ 32), in some order. (As
-// asm with two operands of its own: the builtin with one value for both
-// gives one register for both results. The wait states are the ones that a
-// lane swap needs after a vector write.)
-__device__ inline void swap16(float& x, float& y) { asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y)); }
-__device__ inline void swap32(float& x, float& y) { asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y)); }
-
 // Maximum and sum over the four lanes l % 16 + 16 i, the same in each.
 __device__ inline float quad_max(float x) {
   float y = x;
