@@ -90,7 +90,18 @@ size_t route_ws(const hga_config_t* c, int64_t n_q) {
 // on the early chunks), so it is split over two head subsets whose partials a
 // second kernel sums. (1,024-token segments of the 16K step: two subsets
 // win below 6 k_c history chunks, one above; four never won.)
-int bwd_parts(const hga_config_t* c, int64_t q_begin) {
+//
+// Such a call with few heads or few rows is split further, up to one query head
+// per item, while its dK/dV and dQ workgroups still run at once (one per CU):
+// its time is the longest item's chain of (block, query head) steps. Past 256
+// workgroups a second round costs more than a short chain saves, so only
+// chains of 32 steps and more go there. Two subsets against four: float32,
+// 1,024 rows, 8/2 heads 194 and 107 us; bf16, 1,024 rows, 8/2 heads 60 and 38;
+// 16/4 heads (320 workgroups, 32 steps) 63 and 50; 512 rows, 32/8 heads (320
+// workgroups, 16 steps) 40 and 47. With much history the items are short and
+// the combining pass costs more than a split saves (512 rows at 15,360, 32/8
+// heads: 31 us in one item, 44 in two).
+int bwd_parts(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_begin) {
   const int G = c->n_q_heads / c->n_kv_heads;
   if (c->bwd_kv_parts == 1) return 1;
   if (c->bwd_kv_parts == 2) return G >= 2 ? 2 : 1;
@@ -98,7 +109,17 @@ int bwd_parts(const hga_config_t* c, int64_t q_begin) {
   const int64_t first = (c->sink_tokens + kChunk - 1) / kChunk;
   const int64_t h0 = ls > 0 && ls / kChunk > first ? ls / kChunk - first : 0;  // history candidates
   const int64_t kc = c->top_chunks > 0 ? c->top_chunks : 1;
-  return h0 < 6 * kc && G >= 2 ? 2 : 1;
+  if (h0 >= 6 * kc || G < 2) return 1;
+  const int64_t n_qb = n_q / kChunk;
+  const int64_t n_kv = (q_begin + n_q - grad_begin) / kChunk * c->n_kv_heads;
+  const int64_t n_dq = n_qb * c->n_kv_heads * (G > 4 ? G / 4 : 1);
+  int p = 2;
+  while (p < G) {
+    const int64_t wgs = 2 * p * n_kv + n_dq;
+    if (wgs > 320 || (wgs > 256 && n_qb * (G / p) < 32)) break;
+    p *= 2;
+  }
+  return p;
 }
 
 // Backward workspace: D = rowsum(dO * O) of every (query row, query head),
@@ -107,7 +128,7 @@ size_t bwd_dvec_bytes(const hga_config_t* c, int64_t n_q) {
   return ((size_t)n_q * c->n_q_heads * sizeof(float) + 255) / 256 * 256;
 }
 size_t bwd_ws(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_begin) {
-  const int p = bwd_parts(c, q_begin);
+  const int p = bwd_parts(c, q_begin, n_q, grad_begin);
   const int64_t rows = q_begin + n_q - grad_begin;
   const size_t parts = p == 1 ? 0 : (size_t)2 * p * rows * c->n_kv_heads * c->head_dim * sizeof(float);
   return bwd_dvec_bytes(c, n_q) + parts;
@@ -312,7 +333,7 @@ static hga_status_t attend_bwd_impl(const hga_config_t* cfg, const void* Q, hga_
     a.Vact = V; a.va_tok = vs.token; a.va_head = vs.head;
     a.act_begin = 0;
   }
-  a.kv_parts = bwd_parts(cfg, q_begin);
+  a.kv_parts = bwd_parts(cfg, q_begin, n_q, grad_begin);
   a.part_out = a.kv_parts > 1
       ? reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_dvec_bytes(cfg, n_q)) : nullptr;
   const hipError_t e = r_cap > 0 ? hga::launch_attend_gathered_bwd(a, cfg->dtype == HGA_BF16, cfg->head_dim,

@@ -129,6 +129,7 @@ __device__ __forceinline__ void dq_role(const AttnArgs& a, int wg, char* smem) {
       // masked scores become -inf, whose exponential is exactly 0: a loop of
       // its own under the uniform test, which unmasked tiles branch around
       if (need_mask) {
+        asm volatile("");  // keeps it a branch: the second half's became selects in every tile
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
           const int pos = tile * 64 + 32 * t + 8 * (v >> 2) + 4 * hh + (v & 3);
@@ -320,8 +321,9 @@ struct StepRegs {
   // the compiler wait for it, and for every load issued before it)
   float lse, dd;
 
-  __device__ inline void load(const AttnArgs& a, const int* s_blk, int step, int hq0, int gh, int tid) {
-    load_at(a, s_blk[step / gh], hq0 + step % gh, tid);
+  // step = (listed block, one of 1 << gsh query heads)
+  __device__ inline void load(const AttnArgs& a, const int* s_blk, int step, int hq0, int gsh, int tid) {
+    load_at(a, s_blk[step >> gsh], hq0 + (step & ((1 << gsh) - 1)), tid);
   }
   __device__ inline void load_at(const AttnArgs& a, int bb, int hq, int tid) {
 #pragma unroll
@@ -506,7 +508,10 @@ __device__ __forceinline__ void dkdv_role(const AttnArgs& a, int wg, char* smem)
   const int part = wg / (a.n_kv_heads * a.n_act_chunks);
   const int64_t chunk = a.grad_begin / 64 + cw;
   const int64_t ktok = chunk * 64 + 32 * kh + l32;  // this lane's key token
-  const int gh = a.gqa / a.kv_parts;               // query heads visited per block
+  // query heads visited per block: a power of two, so that a step's block and
+  // head are a shift and a mask, not two divisions by a runtime count
+  const int gh = a.gqa / a.kv_parts;
+  const int gsh = 31 - __builtin_clz(gh);
   const int hq0 = h * a.gqa + part * gh;
 
   // Everything the first step needs is requested at once: when the chunk's
@@ -561,20 +566,20 @@ __device__ __forceinline__ void dkdv_role(const AttnArgs& a, int wg, char* smem)
       s_blk[wbase + before] = b;
       s_mask[wbase + before] = m;
     }
-    const int n_steps = n_list * gh;
+    const int n_steps = n_list << gsh;
     __syncthreads();
     if (n_steps == 0) continue;
 
-    if (!(early && base == b_first)) sr0.load(a, s_blk, 0, hq0, gh, tid);  // else already requested
+    if (!(early && base == b_first)) sr0.load(a, s_blk, 0, hq0, gsh, tid);  // else already requested
     // Slot refills are unconditional, on step indices clamped to the last
     // step (a repeated step is loaded and never stored): conditional ones
     // made the compiler wait for both slots before storing either.
-    sr1.load(a, s_blk, min(1, n_steps - 1), hq0, gh, tid);
+    sr1.load(a, s_blk, min(1, n_steps - 1), hq0, gsh, tid);
     // step 1's loads stay ahead of step 2's: the loop's stores wait for one
     // slot's loads only when the older slot is always the one stored first
     asm volatile("" ::: "memory");
     sr0.store(smem, tid);
-    sr0.load(a, s_blk, min(2, n_steps - 1), hq0, gh, tid);
+    sr0.load(a, s_blk, min(2, n_steps - 1), hq0, gsh, tid);
     __syncthreads();
     // Iteration i: role 0 runs step i; role 1 runs step i - 1 with PIPE (its
     // P was handed over in iteration i - 1), else step i after a barrier.
@@ -585,7 +590,7 @@ __device__ __forceinline__ void dkdv_role(const AttnArgs& a, int wg, char* smem)
   {                                                                                                 \
     const int it_ = (IT);                                                                           \
     const int sj_ = SL::PIPE && role == 1 ? it_ - 1 : it_; /* this wave's step */                  \
-    const int e_ = sj_ / gh;                                                                        \
+    const int e_ = sj_ >> gsh;                                                                      \
     const int64_t bs_ = sj_ >= 0 && sj_ < n_steps ? a.q_begin + (int64_t)s_blk[e_] * 64 : 0;         \
     /* the pair's 32 keys x 32 queries hold a visible entry (with PIPE an */                        \
     /* empty one is skipped by both waves: P and dS are 0 there) */                                 \
@@ -604,7 +609,7 @@ __device__ __forceinline__ void dkdv_role(const AttnArgs& a, int wg, char* smem)
       dkdv_acc<T, D>(st, w, qh, role, lane, acc);                                                   \
     }                                                                                               \
     if (it_ + 1 < n_steps) NEXT.store(smem + ((it_ + 1) % SL::NST) * STAGE, tid); /* step it+1 */    \
-    NEXT.load(a, s_blk, min(it_ + 3, n_steps - 1), hq0, gh, tid);         /* refill: step it+3 */    \
+    NEXT.load(a, s_blk, min(it_ + 3, n_steps - 1), hq0, gsh, tid);         /* refill: step it+3 */    \
     __syncthreads();                                                                                \
   }
     // Whole pairs in the loop and an odd last iteration after it: a loop
