@@ -69,12 +69,26 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
   const char* Vb = static_cast<const char*>(a.V);
   const int64_t k_head_b = (int64_t)wc.h * a.k_head * EB, v_head_b = (int64_t)wc.h * a.v_head * EB;
 
+  // The wave's 32 query rows: bf16 goes through the wave's share of the stages
+  // before the first tile does (131,072 queries: 1,612 us with direct loads,
+  // 1,579 so). float32 rows would not fit, and with LATE the barrier that this
+  // takes costs what it gains: there the fragments are loaded directly.
+  constexpr bool QL = EB == 2 && !LATE;
   Frag qf[NKS];
+  RowFrags<T, D> qrows;
   {
-    const char* qrow = Qb + ((int64_t)row * a.q_tok + (int64_t)hq * a.q_head) * EB;
+    const char* q0 = Qb + (((int64_t)wc.b * 64 + (wave & 1) * 32) * a.q_tok + (int64_t)hq * a.q_head) * EB;
+    if constexpr (QL) {
+      static_assert(2 * GW * RowFrags<T, D>::kBytes <= 2 * STAGE, "the waves' rows fit the stages");
+      qrows.load(q0, a.q_tok * EB, lane);
+    } else {
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) qf[ks] = EL::load_frag(qrow + (ks * KS + E * hh) * EB);
+      for (int ks = 0; ks < NKS; ++ks) qf[ks] = EL::load_frag(q0 + l32 * a.q_tok * EB + (ks * KS + E * hh) * EB);
+    }
   }
+  auto take_queries = [&] {
+    if constexpr (QL) qrows.fragments(smem + wave * RowFrags<T, D>::kBytes, lane, qf);
+  };
   // CMP: K and V are the compact copies of hga_gather_routed, rows of this
   // (block, kv head)'s routed set in tile order, padding rows zero
   const int64_t cslot = CMP ? ((int64_t)wc.b * a.n_kv_heads + wc.h) * a.r_cap * D * EB : 0;
@@ -201,7 +215,8 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
     gather_w(kv0, 0);  // always a window tile
     if (nwt > 1) gather_w(kv1, 1);
     take_routing();
-    sync();  // the routing row's LDS copy
+    take_queries();
+    sync();  // the routing row's LDS copy is there, the waves' query rows have been read
     const int last = ntl - 1;
     if (nwt <= 1) gather(kv1, min(1, last));
     put(kv0, smem);
@@ -351,7 +366,7 @@ constexpr bool three_per_simd() { return Elem<T>::kBytes == 2 && D == 64 && GW =
 // a tile's LDS reads, matrix products and exponentials take about as long
 // each; they overlap only as far as the two waves are apart. 131,072 queries,
 // Qwen3-8B layer, 576 routed keys: 1,938 us when every tile waited for its own
-// gather and the softmax maximum went through the LDS crossbar, 1,590 us (737
+// gather and the softmax maximum went through the LDS crossbar, 1,579 us (742
 // TFLOP/s) now.
 template <typename T, int D, int GW, bool PREC, bool CMP>
 __global__ __launch_bounds__(128 * GW) __attribute__((amdgpu_waves_per_eu(three_per_simd<T, D, GW>() ? 3 : 1))) void attend_fwd_kernel(AttnArgs a) {
@@ -421,7 +436,7 @@ static hipError_t fwd_dispatch(const AttnArgs& a, hipStream_t s) {
   // fill it instead. bf16 with d = 64 takes two heads always: three such
   // workgroups fit a CU and hide each other's start and end (10,048 queries,
   // G = 8: 50 us against 60 with four heads and one workgroup per CU; at
-  // d = 128, where two fit, 131,072 queries take 1,759 against 1,590).
+  // d = 128, where two fit, 131,072 queries took 1,759 against 1,590).
   int gw = a.gqa >= 4 ? 4 : a.gqa;
   if (gw == 4 && three_per_simd<T, D, 2>()) gw = 2;
   if (gw == 4 && (int64_t)a.n_qb * a.n_kv_heads * (a.gqa / 4) < 256) gw = 2;

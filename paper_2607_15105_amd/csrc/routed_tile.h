@@ -273,6 +273,39 @@ struct KVRegs {
   }
 };
 
+// One wave's 32 rows (at `base`, `stride` bytes apart) as row operands: lane l's
+// fragments of row l % 32. Loaded with a row's 16-byte pieces on consecutive
+// lanes and handed over through the wave's own LDS (32 row pitches at `buf`):
+// with each lane loading its own fragments, neighbouring lanes lie in
+// different rows and every one of them is a cache access of its own.
+template <typename T, int D>
+struct RowFrags {
+  using TL = Tile<T, D>;
+  using Frag = typename Elem<T>::Frag;
+  static constexpr int EB = Elem<T>::kBytes, CPR = D * EB / 16, NJ = 32 * CPR / 64;
+  static constexpr int kBytes = 32 * TL::kRowPitch;
+  u32x4 x[NJ];
+  __device__ inline void load(const char* base, int64_t stride, int lane) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int it = lane + 64 * j;
+      x[j] = *reinterpret_cast<const u32x4*>(base + (it / CPR) * stride + (it % CPR) * 16);
+    }
+  }
+  __device__ inline void fragments(char* buf, int lane, Frag (&f)[D / Elem<T>::KSTEP]) const {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int it = lane + 64 * j;
+      *reinterpret_cast<u32x4*>(buf + TL::row_off(it / CPR, (it % CPR) * 16 / EB)) = x[j];
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int ks = 0; ks < D / Elem<T>::KSTEP; ++ks)
+      f[ks] = Elem<T>::load_frag(buf + TL::row_off(lane & 31, ks * Elem<T>::KSTEP + Elem<T>::E * (lane >> 5)));
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+
 // Decode a workgroup id into (query block, head slice, kv head). The kv head
 // is the fastest index so that consecutive workgroups (dispatched round-robin
 // over the 8 XCDs) keep each kv head on one XCD when Hkv == 8, where its
