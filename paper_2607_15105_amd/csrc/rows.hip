@@ -108,8 +108,13 @@ struct RowsRoute {
 // 131K, 2,027 candidates: 34 us with four waves and one selection by ranks,
 // 23 us so. The scoring takes half of it: the CU's float64 conversions and the
 // descriptor's LDS reads, not the summary rows; four load slots were no faster.)
-template <typename T, int D, int RB, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(RB == 1 && NT == 256 ? 1 : 4))) void
+// WHOLE (one row, 256 threads): a summary row's loads all in flight at once, one
+// workgroup per CU. It is the shortest for a workgroup on its own, so it serves
+// calls with at most one per CU (one row at 16K: 9.3 us against 12.8 with ranks);
+// with more, the sixteen-element units let four share a CU (64 rows at 16K,
+// 512 workgroups: 18 us whole, 10.9 in units; 15.4 with ranks).
+template <typename T, int D, int RB, int NT, bool WHOLE>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(WHOLE ? 1 : 4, 8))) void
 route_rows_kernel(RouteArgs a, int64_t n_rows, int stride) {
   constexpr int EB = Elem<T>::kBytes;
   constexpr int RR = RowsRoute<RB>::RR;
@@ -163,7 +168,7 @@ route_rows_kernel(RouteArgs a, int64_t n_rows, int stride) {
     for (int i0 = 0; i0 < nr; i0 += NT) {
       const int i = i0 + tid;
       double v[RB];
-      if constexpr (RB == 1 && NT == 256) v[0] = summary_dot<D>(cs, r0 + min(i, nr - 1), a.chunk_cap, s_q[0]);
+      if constexpr (WHOLE) v[0] = summary_dot<D>(cs, r0 + min(i, nr - 1), a.chunk_cap, s_q[0]);
       else summary_dots<D, RB>(cs, r0 + min(i, nr - 1), a.chunk_cap, s_q, nv, v);
       if (i < nr) {
 #pragma unroll
@@ -233,7 +238,7 @@ route_rows_kernel(RouteArgs a, int64_t n_rows, int stride) {
       const int fa = f0 + tid, w = fa / gslot, f = fa - w * gslot;
       if (w < nv && f < (min(a.top_chunks, n_cand_of(w)) << gpc_shift)) {
         const int64_t j = ((int64_t)s_chunks[w][f >> gpc_shift] << gpc_shift) + (f & gmask);
-        if constexpr (RB == 1 && NT == 256) {
+        if constexpr (WHOLE) {
           dyn[w * stride + f] = no_nan(summary_dot<D>(gs, j, a.group_cap, s_q[w]));
         } else {
           double v[1];
@@ -273,21 +278,20 @@ hipError_t launch_route_rows(const RouteArgs& a, int64_t n_rows, int n_cand_max,
   const int stride = nc > group_cand ? nc : group_cand;
   const size_t lds = (size_t)rb * stride * sizeof(double);
   const dim3 grid((unsigned)((n_rows + rb - 1) / rb * a.n_kv_heads));
-#define HGA_RR(T, D, RB, NT) \
-  hipLaunchKernelGGL((route_rows_kernel<T, D, RB, NT>), grid, dim3(NT), lds, s, a, n_rows, stride)
-  if (rb == 1 && n_cand_max > 256) {
-    if (!bf16) HGA_RR(float, 64, 1, 1024);
-    else if (head_dim == 64) HGA_RR(__bf16, 64, 1, 1024);
-    else HGA_RR(__bf16, 128, 1, 1024);
-  } else if (rb == 1) {
-    if (!bf16) HGA_RR(float, 64, 1, 256);
-    else if (head_dim == 64) HGA_RR(__bf16, 64, 1, 256);
-    else HGA_RR(__bf16, 128, 1, 256);
-  } else {
-    if (!bf16) HGA_RR(float, 64, 4, 256);
-    else if (head_dim == 64) HGA_RR(__bf16, 64, 4, 256);
-    else HGA_RR(__bf16, 128, 4, 256);
-  }
+#define HGA_RR(T, D, RB, NT, WHOLE) \
+  hipLaunchKernelGGL((route_rows_kernel<T, D, RB, NT, WHOLE>), grid, dim3(NT), lds, s, a, n_rows, stride)
+#define HGA_RRT(RB, NT, WHOLE)                          \
+  do {                                                  \
+    if (!bf16) HGA_RR(float, 64, RB, NT, WHOLE);        \
+    else if (head_dim == 64) HGA_RR(__bf16, 64, RB, NT, WHOLE); \
+    else HGA_RR(__bf16, 128, RB, NT, WHOLE);            \
+  } while (0)
+  const bool alone = n_rows * a.n_kv_heads <= 256;  // one workgroup per CU at most
+  if (rb == 4) HGA_RRT(4, 256, false);
+  else if (!alone) HGA_RRT(1, 256, false);
+  else if (n_cand_max > 256) HGA_RRT(1, 1024, false);
+  else HGA_RRT(1, 256, true);
+#undef HGA_RRT
 #undef HGA_RR
   return hipGetLastError();
 }
