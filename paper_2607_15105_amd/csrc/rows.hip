@@ -12,11 +12,12 @@
 // closed before the local window) and attends only tokens up to its own
 // position, so rows after it are never read.
 //
-// Routing: one workgroup of four waves per (four consecutive query rows, or
-// one row when the call is too small to fill the chip that way, kv head). A row's descriptor is the exact
+// Routing: one workgroup per (four consecutive query rows, or one row when the
+// call is too small to fill the chip that way, kv head), of four waves, or of
+// sixteen for a row with a long candidate list. A row's descriptor is the exact
 // float64 mean of its G query-head rows; chunk and group scores (one
 // candidate per thread, against every row of the workgroup) are float64 FMA
-// chains over the float32 summaries, ranked by wave_top_k, one wave per row
+// chains over the float32 summaries, selected by wave_top_k, one wave per row
 // (larger score first, lower index on ties; sets returned ascending).
 //
 // Attention, bf16: rows of one block in groups of up to 16 (row, query head)
