@@ -48,7 +48,7 @@ typedef enum {
   HGA_OK = 0,
   HGA_ERR_INVALID_ARG = -1, /* null pointer, bad range, divisibility, alignment */
   HGA_ERR_UNSUPPORTED = -2, /* valid problem outside what the library implements */
-  HGA_ERR_WORKSPACE = -3,   /* workspace missing or smaller than hga_workspace_size */
+  HGA_ERR_WORKSPACE = -3,   /* workspace missing or too small for the call */
   HGA_ERR_HIP = -4          /* a HIP launch or runtime call failed */
 } hga_status_t;
 
@@ -69,11 +69,12 @@ typedef struct {
   float softmax_scale;   /* <= 0 selects 1/sqrt(head_dim)                              */
   hga_dtype_t dtype;     /* element type of Q, K, V, O and dO                          */
   int32_t bwd_kv_parts;  /* dK/dV work items per (active chunk, kv head) in            */
-                         /* hga_attend_bwd: 0 = the library's choice (two or more     */
-                         /* query-head subsets when the call has little routable     */
-                         /* history, which shortens one call), 1 = one (least total work, for       */
-                         /* callers that overlap several backward calls), 2 = two    */
-                         /* when Hq / Hkv >= 2; other values HGA_ERR_INVALID_ARG     */
+                         /* hga_attend_bwd: 0 = the library's choice (two, four or   */
+                         /* eight query-head subsets when the call has little        */
+                         /* routable history, which shortens one call), 1 = one      */
+                         /* (least total work, for callers that overlap several      */
+                         /* backward calls), 2 = two when Hq / Hkv >= 2; other       */
+                         /* values HGA_ERR_INVALID_ARG                               */
 } hga_config_t;
 
 /* Element strides of a token-major tensor; the head_dim axis is contiguous.
@@ -246,16 +247,22 @@ hga_status_t hga_attend_gathered_fwd(const hga_config_t* cfg, const void* Q, hga
  *              (never 0): D of every (query row, query head), n_q * Hq
  *              floats rounded up to 256 bytes, then, when the call starts
  *              with little routable history (fewer than 6 * top_chunks
- *              candidate chunks before its first block), the partial dK/dV
- *              sums of 2 subsets of the query heads: most routed keys then
- *              lie in the active segment and the dK/dV work of each chunk is
- *              split over those subsets. Its contents need no
- *              initialisation.
+ *              candidate chunks before its first block) and Hq / Hkv >= 2,
+ *              the partial dK/dV sums of p subsets of the query heads, 2 * p
+ *              * (q_begin + n_q - grad_begin) * Hkv * d floats: most routed
+ *              keys then lie in the active segment and the dK/dV work of
+ *              each chunk is split over those subsets. p is 2, or 4 or 8 for
+ *              calls of few rows and heads; it depends on the heads, q_begin,
+ *              n_q and grad_begin, so a shorter call's size may be the
+ *              larger. A buffer that holds fewer subsets, down to two, is
+ *              taken too (one sized for a longer call of the same q_begin
+ *              and grad_begin always is): the call then splits into as many
+ *              as fit. Its contents need no initialisation.
  * A first kernel forms D = rowsum(dO * O) of every row; one launch then
  * computes dQ (query-major) and dK/dV (key-major) side by side. dK/dV are
  * accumulated in fixed order (no atomics; the split partials are summed in a
  * fixed order by a third kernel): results are bitwise reproducible run to
- * run. With bf16 inputs dS enters dQ = dS K as a pair of bf16 values
+ * run, for the same number of subsets. With bf16 inputs dS enters dQ = dS K as a pair of bf16 values
  * (hi + lo), since dQ scales dS by raw key magnitudes.
  */
 hga_status_t hga_attend_bwd(const hga_config_t* cfg, const void* Q, hga_strides_t qs,

@@ -127,11 +127,23 @@ int bwd_parts(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_
 size_t bwd_dvec_bytes(const hga_config_t* c, int64_t n_q) {
   return ((size_t)n_q * c->n_q_heads * sizeof(float) + 255) / 256 * 256;
 }
-size_t bwd_ws(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_begin) {
-  const int p = bwd_parts(c, q_begin, n_q, grad_begin);
+size_t bwd_ws_of(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_begin, int p) {
   const int64_t rows = q_begin + n_q - grad_begin;
   const size_t parts = p == 1 ? 0 : (size_t)2 * p * rows * c->n_kv_heads * c->head_dim * sizeof(float);
   return bwd_dvec_bytes(c, n_q) + parts;
+}
+size_t bwd_ws(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_begin) {
+  return bwd_ws_of(c, q_begin, n_q, grad_begin, bwd_parts(c, q_begin, n_q, grad_begin));
+}
+// The split of a call with `bytes` of workspace: the one above, or, where that
+// does not fit, the finest that does; 0 if not even two subsets do (one, where
+// the call does not split). The finer splits belong to short calls, so a short
+// call can want more than a longer one (32/8 heads, d = 128: 256 rows 8.4 MB,
+// 448 rows 7.4 MB), and a buffer sized for the longer one has to do for both.
+int bwd_parts_in(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_begin, size_t bytes) {
+  int p = bwd_parts(c, q_begin, n_q, grad_begin);
+  while (p > 2 && bwd_ws_of(c, q_begin, n_q, grad_begin, p) > bytes) p /= 2;
+  return bwd_ws_of(c, q_begin, n_q, grad_begin, p) <= bytes ? p : 0;
 }
 
 float eff_scale(const hga_config_t* c) {
@@ -310,8 +322,8 @@ static hga_status_t attend_bwd_impl(const hga_config_t* cfg, const void* Q, hga_
   if (!lse || !n_sel_groups || (cfg->top_groups > 0 && !sel_groups)) return HGA_ERR_INVALID_ARG;
   if (!dQ || !dK || !dV || !aligned16(dQ) || !aligned16(dK) || !aligned16(dV))
     return HGA_ERR_INVALID_ARG;
-  const size_t need = bwd_ws(cfg, q_begin, n_q, grad_begin);
-  if (!workspace || workspace_bytes < need || !aligned16(workspace)) return HGA_ERR_WORKSPACE;
+  const int parts = bwd_parts_in(cfg, q_begin, n_q, grad_begin, workspace_bytes);
+  if (!workspace || parts == 0 || !aligned16(workspace)) return HGA_ERR_WORKSPACE;
   AttnArgs a = attn_args(cfg, Q, qs, K, ks, V, vs, q_begin, n_q, sel_groups, n_sel_groups);
   if (o_f32 && !aligned16(o_f32)) return HGA_ERR_INVALID_ARG;
   a.O = O; a.o_tok = os.token; a.o_head = os.head;
@@ -333,7 +345,7 @@ static hga_status_t attend_bwd_impl(const hga_config_t* cfg, const void* Q, hga_
     a.Vact = V; a.va_tok = vs.token; a.va_head = vs.head;
     a.act_begin = 0;
   }
-  a.kv_parts = bwd_parts(cfg, q_begin, n_q, grad_begin);
+  a.kv_parts = parts;
   a.part_out = a.kv_parts > 1
       ? reinterpret_cast<float*>(static_cast<char*>(workspace) + bwd_dvec_bytes(cfg, n_q)) : nullptr;
   const hipError_t e = r_cap > 0 ? hga::launch_attend_gathered_bwd(a, cfg->dtype == HGA_BF16, cfg->head_dim,
@@ -526,8 +538,7 @@ hga_status_t hga_attend_bwd_noalloc(const hga_config_t* cfg, const void* Q, hga_
   HGA_TRY(check_cfg(cfg));
   HGA_TRY(check_rows(q_begin, n_q));
   if (grad_begin < 0 || grad_begin > q_begin || grad_begin % kChunk != 0) return HGA_ERR_INVALID_ARG;
-  const size_t need = bwd_ws(cfg, q_begin, n_q, grad_begin);
-  if (need > (size_t)HGA_NOALLOC_SCRATCH_BYTES) return HGA_ERR_WORKSPACE;
+  if (bwd_parts_in(cfg, q_begin, n_q, grad_begin, HGA_NOALLOC_SCRATCH_BYTES) == 0) return HGA_ERR_WORKSPACE;
   void* ws = nullptr;
   HGA_TRY(noalloc_scratch(&ws));
   return attend_bwd_impl(cfg, Q, qs, K, ks, V, vs, O, os, o_f32, dO, dos, lse, q_begin, n_q, grad_begin,

@@ -130,6 +130,25 @@ def test_backward_rejects_grad_begin_after_q_begin():
     assert st == -1
 
 
+@pytest.mark.parametrize("hq,hkv,short,longer", [(32, 8, 256, 448), (32, 8, 384, 704), (16, 2, 1024, 4032),
+                                                 (8, 2, 2048, 2112), (8, 1, 512, 512), (32, 8, 1024, 1024)])
+def test_backward_takes_a_buffer_of_two_subsets_or_of_a_longer_call(hq, hkv, short, longer):
+    """What a call that splits its dK/dV work asks of its buffer is two query-head
+    subsets, also where the library would take more: a buffer sized for a longer
+    call, which may split less, does for a shorter one. o_f32 is misaligned, which is
+    looked at after the buffer: no call gets as far as a launch."""
+    c = _cfg(n_q_heads=hq, n_kv_heads=hkv)
+    L = hga.lib()
+    S, Skv = hga.Strides(hq * 128, 128), hga.Strides(hkv * 128, 128)
+    status = lambda size: L.hga_attend_bwd(ctypes.byref(c), FAKE, S, FAKE, Skv, FAKE, Skv, FAKE, S, FAKE + 4, FAKE, S,
+                                           FAKE, 0, short, 0, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, size, None)
+    two = -(-short * hq * 4 // 256) * 256 + 2 * 2 * short * hkv * 128 * 4
+    assert status(hga.workspace_size(c, hga.OP_BWD, 0, short, 0)) == -1
+    assert status(hga.workspace_size(c, hga.OP_BWD, 0, longer, 0)) == -1
+    assert status(two) == -1
+    assert status(two - 1) == -3
+
+
 def test_gather_rejects_short_or_unaligned_slots():
     c = _cfg()  # Ws 64 + Wl 128 + 16 groups of 8 = 320 rows per slot at least
     L = hga.lib()

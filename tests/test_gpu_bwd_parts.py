@@ -40,3 +40,37 @@ def test_library_choice(G, n_kv, n_q, q_begin, d, dtype, parts):
     wl = _wl(G, n_kv, n_q, q_begin, d, dtype)
     assert _parts(wl) == parts
     _full_check(wl, backward=True)
+
+
+def test_a_buffer_sized_for_a_longer_call_takes_a_shorter_one():
+    """32/8 heads from token 0: 256 rows split into four subsets and 448 rows
+    into two, in fewer bytes. In the longer call's buffer the shorter call
+    splits into two, as where the caller asks for two."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    wl = _wl(4, 8, 256, 0, 128, "bf16")
+    hc = P.hcfg_of(wl)
+    two = hga.make_config(32, 8, 128, group_size=wl.group_size, top_chunks=wl.top_chunks, top_groups=wl.top_groups,
+                          sink_tokens=wl.sink_tokens, local_tokens=wl.local_tokens, bwd_kv_parts=2)
+    small, full = (hga.workspace_size(hc, hga.OP_BWD, 0, n, 0) for n in (448, 256))
+    assert hga.workspace_size(two, hga.OP_BWD, 0, 256, 0) < small < full
+    K, V, Q, dO = (P.to_dev(f(wl, 0, 256)) for f in (synth.keys, synth.values, synth.queries, synth.grad_output))
+    cs, gs = hga.alloc_summaries(hc, 256)
+    rb = hga.alloc_route(hc, 0, 256)
+    O, lse = torch.empty_like(Q), torch.empty(256, 32, device="cuda")
+    hga.build_summaries(hc, K, 0, 256, cs, gs)
+    hga.route_attend_fwd(hc, Q, K, V, 0, cs, gs, rb.sel_chunks, rb.sel_groups, rb.n_sel_groups, O, lse, rb.workspace)
+
+    def grads(cfg, size):
+        ws = torch.full((size + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+        out = [torch.empty(256, h, 128, device="cuda") for h in (32, 8, 8)]
+        hga.attend_bwd(cfg, Q, K, V, O, dO, lse, 0, 0, rb.sel_groups, rb.n_sel_groups, *out, ws[:size])
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0xFF).all())  # nothing past the buffer's end
+        return out
+
+    a, b, c = grads(hc, small), grads(two, small), grads(hc, full)
+    for x, y, z in zip(a, b, c):
+        assert torch.equal(x, y)
+        # sums of the same terms in another order: 84 units of float32 rounding
+        assert (x - z).abs().max() <= 1e-5 * z.abs().max()
