@@ -312,7 +312,9 @@ hga_status_t hga_route_rows(const hga_config_t* cfg, const void* Q, hga_strides_
  * hga_attend_rows_fwd - exact-token attention (Sec. 2.1 item 3) of each query
  * row over its own routed set from hga_route_rows: the sink window of its
  * block, its selected groups, and its block's local window up to and
- * including the row's position. Keys after the row are never read.
+ * including the row's position. Keys after the row never enter its result,
+ * infinities and NaN among them (those of the call's own later rows may be
+ * read).
  *
  *   Q          rows [0, n_q), strides qs (row i = position q_begin + i).
  *   K, V       rows [0, q_begin + n_q), strides ks / vs.
@@ -321,8 +323,11 @@ hga_status_t hga_route_rows(const hga_config_t* cfg, const void* Q, hga_strides_
  *   lse        float32 [n_q][Hq], natural log.
  *   o_f32      optional (may be NULL) float32 [n_q][Hq][d], dense: O before
  *              its rounding to cfg->dtype, for hga_attend_rows_bwd.
- * Scores, softmax and accumulation in float32. With bf16 inputs P is rounded
- * to bf16 before P.V (as in hga_attend_fwd); with float32 inputs it is not.
+ * Scores, softmax and accumulation in float32. With bf16 inputs P enters P.V
+ * as a pair of bf16 values (hi + lo, to about 2^-17), whether o_f32 is given or
+ * not; with float32 inputs it is not rounded. Three forms of the kernel share
+ * calls of few, more and many rows, so a row's result can differ in its last
+ * float32 bits (O before its rounding) with the number of rows in the call.
  */
 hga_status_t hga_attend_rows_fwd(const hga_config_t* cfg, const void* Q, hga_strides_t qs,
                                  const void* K, hga_strides_t ks, const void* V, hga_strides_t vs,

@@ -10,7 +10,7 @@
 // A query keeps the windows and the candidate chunks of the 64-token block
 // holding it (sink window, local window ending at the block end, chunks
 // closed before the local window) and attends only tokens up to its own
-// position, so rows after it are never read.
+// position: keys after it never enter its result.
 //
 // Routing: one workgroup per (four consecutive query rows, or one row when the
 // call is too small to fill the chip that way, kv head), of four waves, or of
@@ -523,8 +523,14 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
 //  - S^T = K Q^T: K rows from LDS (A operand), the pairs' Q rows in registers.
 //  - online softmax: lane l holds 8 scores of pair l % 16; the maximum over
 //    the four lanes of a pair goes by lane swaps.
-//  - O^T += V^T P^T: P^T from the registers that hold S^T (bf16), V from LDS
-//    through the transpose load.
+//  - O^T += V^T P^T: P^T from the registers that hold S^T, V from LDS through
+//    the transpose load. P enters as a bf16 hi + lo pair. As one bf16 value the
+//    lazily raised maximum would leave the heaviest key's P unrepresentable,
+//    which is exactly 1 under an exact maximum: 1.6e-3 of O's norm (float32
+//    copy, 320 keys) against 1.3e-3, and the backward's D carries it on to dQ.
+//    The exact maximum alone gives back 1.2e-3 where several waves share a row
+//    and each has its own, but not with a wave per group. The pair gives
+//    3e-6, for 0 to 4% of the time (9% with 8,192 keys a row).
 // One register set of K and one of V: the next step's rows go out when these
 // are in LDS (one buffer per wave, K and then V).
 //
@@ -557,6 +563,19 @@ __device__ inline float quad_sum(float x) {
   x = y = x + y;
   swap32(x, y);
   return x + y;
+}
+
+// A product that no sum takes up unrounded.
+__device__ inline float mul_rounded(float x, float y) {
+#pragma clang fp contract(off)
+  return x * y;
+}
+
+// Natural logarithm of l 2^m, rounded once: log2 of l's mantissa is below 1 in
+// size, and the sum is taken in float64.
+__device__ inline float lse_of(float m, float l) {
+  const double e = (double)m + (double)__builtin_amdgcn_frexp_expf(l);
+  return (float)((e + (double)__log2f(__builtin_amdgcn_frexp_mantf(l))) * 0.69314718055994530942);
 }
 
 // A group of rows and its key lists. List 0 is shared (n_sh keys: the sink
@@ -690,6 +709,7 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_wave
   constexpr int VP = D * 2 + 32;   // and of a V row: a transpose load's eight rows start 8 banks apart
   constexpr int NW = KW == 1 ? 4 : KW;
   constexpr int NG = KW == 1 ? 4 : 1;  // groups per workgroup
+  constexpr int NV = 4;  // V tiles at a time: a tile's two products are not one after the other
   static_assert(RPW * G <= 16, "a group's pairs are the columns of one product");
   // each wave's K, then V rows of its current step; with KW > 1, at the end, its O
   __shared__ __attribute__((aligned(16))) char s_v[NW][kRowsStep * VP];
@@ -714,7 +734,6 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_wave
   const char* Vb = static_cast<const char*>(a.V) + (int64_t)h * a.v_head * 2;
   const int64_t k_stride = a.k_tok * 2, v_stride = a.v_tok * 2;
   const float c = a.scale_log2;
-  const float lazy = 8.0f / c;  // the maximum is raised when it grows by more than 2^8
   char* sv = s_v[wave];
   const char* tr = sv + (4 * quad + (pr >> 2)) * VP + 8 * (pr & 3);  // this lane's transpose-load address
   char* Ob = static_cast<char*>(a.Out);
@@ -740,7 +759,8 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_wave
     // with few rows the routing and query rows go ahead of every wave's K and V rows
     if constexpr (KW > 1) __builtin_amdgcn_s_barrier();
 
-    // this lane's pair: running maximum (raw scores), sum, O
+    // this lane's pair: running maximum (scores in log2 units, as rounded to
+    // float32: every p, correction and the LSE are relative to that), sum, O
     float m = -__builtin_inff(), l = 0.0f;
     f32x4 o[NT];
 #pragma unroll
@@ -783,37 +803,44 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_wave
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[t][i]);
-      mx = quad_max(mx);
-      const bool raise = mx > m + lazy;
+      mx = mul_rounded(quad_max(mx), c);
+      const bool raise = mx > m + 8.0f;  // the maximum is raised when it grows by more than 2^8
       if (__any(raise)) {
-        const float mn = raise ? mx : m;
-        const float corr = m == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f((m - mn) * c);
-        if (raise) {
-          m = mn;
-          l *= corr;
-        }
-        const float f = raise ? corr : 1.0f;
+        const float f = raise ? __builtin_amdgcn_exp2f(m - mx) : 1.0f;
+        if (raise) m = mx;
+        l *= f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) o[t] *= f;
       }
-      const float mc = m == -__builtin_inff() ? 0.0f : m * c;  // nothing attended yet: every p is 0
-      bf16x8 pf;
+      const float mc = m == -__builtin_inff() ? 0.0f : m;  // nothing attended yet: every p is 0
+      bf16x8 hi, lo;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const float p = __builtin_amdgcn_exp2f(fmaf(s[t][i], c, -mc));
           l += p;
-          pf[4 * t + i] = (__bf16)p;
+          hi[4 * t + i] = (__bf16)p;
+          lo[4 * t + i] = (__bf16)(p - (float)hi[4 * t + i]);
         }
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(tr + 32 * t));
-        const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(tr + 16 * VP + 32 * t));
-        typedef short s16x8 __attribute__((ext_vector_type(8)));
-        const s16x8 xy = __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
-        o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xy), pf, o[t], 0, 0, 0);
+      for (int t0 = 0; t0 < NT; t0 += NV) {
+        bf16x8 vt[NV];
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+          const int t = t0 + j;
+          const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(tr + 32 * t));
+          const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4)(tr + 16 * VP + 32 * t));
+          typedef short s16x8 __attribute__((ext_vector_type(8)));
+          vt[j] = __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
+        }
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+          o[t0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[j], hi, o[t0 + j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+          o[t0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[j], lo, o[t0 + j], 0, 0, 0);
       }
       __builtin_amdgcn_wave_barrier();
     };
@@ -857,7 +884,7 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_wave
     if constexpr (KW == 1) {
       if (!bad && pr < nr * G) {
         const float inv = 1.0f / l;
-        if (quad == 0) a.lse[row * a.n_q_heads + hq] = (m * c + __log2f(l)) * kLn2;
+        if (quad == 0) a.lse[row * a.n_q_heads + hq] = lse_of(m, l);
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           const int d0 = 16 * t + 4 * quad;
@@ -894,7 +921,7 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_wave
         float den = 0.0f;
 #pragma unroll
         for (int w = 0; w < KW; ++w) {
-          const float f = s_m[w][p] == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f((s_m[w][p] - M) * c);
+          const float f = s_m[w][p] == -__builtin_inff() ? 0.0f : __builtin_amdgcn_exp2f(s_m[w][p] - M);
           num += f * *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(s_v[w]) + p * D + d0);
           den = fmaf(f, s_l[w][p], den);
         }
@@ -905,7 +932,7 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_wave
             uint2{float_to_bf16_bits(v[0]) | (float_to_bf16_bits(v[1]) << 16),
                   float_to_bf16_bits(v[2]) | (float_to_bf16_bits(v[3]) << 16)};
         if (a.o32) *reinterpret_cast<f32x4*>(a.o32 + (r * a.n_q_heads + hp) * D + d0) = v;
-        if (d0 == 0) a.lse[r * a.n_q_heads + hp] = (M * c + __log2f(den)) * kLn2;
+        if (d0 == 0) a.lse[r * a.n_q_heads + hp] = lse_of(M, den);
       }
       if constexpr (RPW > 1) __syncthreads();  // the buffers are read: a further pass may overwrite them
     }

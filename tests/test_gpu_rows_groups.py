@@ -123,3 +123,41 @@ def test_rows_dq_of_rows_not_attending_a_non_finite_key(n_q):
         assert (x - y)[clean].abs().max() <= 1e-5 * x[clean].abs().max()
         assert not torch.isfinite(y[sees].sum(-1)).any()
     assert (dq(K, None) - dq(K, o32)).abs().max() <= 2e-2
+
+
+# the three forms, by rows: twelve waves per row, four waves per group, a wave per group
+@pytest.mark.parametrize("tails", [False, True])
+@pytest.mark.parametrize("n_q", [20, 90, 600])
+def test_rows_float32_output_keeps_the_weights(n_q, tails):
+    """The float32 copy of O against float64 on the same routing: P enters P.V
+    as a bf16 hi + lo pair, so no weight is off by more than 2^-17 (7.6e-6);
+    the scores' float32 sums add about 1e-6. A P rounded to bf16 gives 1.2e-3
+    and more. The LSE: half a unit of its own rounding, and the sums'."""
+    wl = synth.Workload("rows_o32", T=2048, n_q_heads=32, n_kv_heads=8, head_dim=128, dtype="bf16", seed=35,
+                        q_begin=1400, n_q=n_q, grad_begin=0, key_offset="student_t" if tails else "normal")
+    hc, end = P.hcfg_of(wl), wl.q_begin + n_q
+    K, V, Q = (P.to_dev(x) for x in (synth.keys(wl, 0, end), synth.values(wl, 0, end),
+                                     synth.queries(wl, wl.q_begin, end)))
+    cs, gs = hga.alloc_summaries(hc, -(-end // 64) * 64)
+    hga.build_summaries(hc, K, 0, end, cs, gs)
+    sc, sg, ns = hga.alloc_route_rows(hc, n_q)
+    hga.route_rows(hc, Q, wl.q_begin, cs, gs, sc, sg, ns)
+    O, lse = torch.empty_like(Q), torch.empty(n_q, 32, device="cuda")
+    o32 = torch.empty(n_q, 32, 128, device="cuda")
+    hga.attend_rows_fwd(hc, Q, K, V, wl.q_begin, sg, ns, O, lse, o32)
+    # every row's set as a mask over the context, in float64
+    pos = wl.q_begin + torch.arange(n_q, device="cuda")
+    tok = torch.arange(end, device="cuda")
+    ls = pos // 64 * 64 + 64 - wl.local_tokens
+    see = ((tok < wl.sink_tokens) | (tok >= ls[:, None]))[:, None].repeat(1, 8, 1)
+    see |= (tok[None, None, :, None] // wl.group_size == sg[:, :, None, :]).any(-1)
+    see &= (tok <= pos[:, None])[:, None]
+    worst = 0.0
+    for h in range(8):
+        q = Q[:, 4 * h:4 * h + 4].double()
+        s = torch.matmul(q, K[:, h].double().T) / 128 ** 0.5
+        s.masked_fill_(~see[:, h][:, None], -float("inf"))
+        want = torch.matmul(torch.softmax(s, -1), V[:, h].double())
+        worst = max(worst, float((o32[:, 4 * h:4 * h + 4] - want).norm() / want.norm()))
+        assert (lse[:, 4 * h:4 * h + 4] - torch.logsumexp(s, -1)).abs().max() <= 3e-6
+    assert worst <= 1e-5
