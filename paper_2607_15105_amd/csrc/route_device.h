@@ -18,6 +18,8 @@
 // score first, lower index on equal scores (NaN scores count as -inf); the
 // selected sets are returned ascending.
 #pragma once
+#include <type_traits>
+
 #include "hga_device.h"
 #include "hga_kernels.h"
 
@@ -261,6 +263,12 @@ __device__ __attribute__((always_inline)) inline int wave_top_k_ranked(const dou
   return lane < k_eff && lane < nsel ? ws.out[lane] : kNoIdx;
 }
 
+__device__ inline uint32_t wave_min_u32(uint32_t x) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) x = min(x, (uint32_t)__shfl_xor((int)x, m, 64));
+  return x;
+}
+
 // Order-preserving 32-bit key of a score: equal scores (-0 and 0 among them)
 // have equal keys, and a larger key means a larger score; scores that round
 // to the same float share a key. 0 is below every score's key.
@@ -273,7 +281,8 @@ __device__ inline uint32_t score_key(double x) {
 // The k-th largest key T of the wave's 64 E keys (k >= 1, at least k of them
 // nonzero), bit by bit from the top with a count of the keys at or above; true
 // if exactly k keys are >= T. It stops at the first T that separates them,
-// usually after the exponent and a few bits of the mantissa.
+// usually after the exponent and a few bits of the mantissa; false: T is the
+// k-th key itself and more than k are >= T.
 template <int E>
 __device__ inline bool kth_key(const uint32_t (&key)[E], int k, uint32_t& T) {
   T = 0;
@@ -304,8 +313,9 @@ __device__ inline void take_keys(const uint32_t (&key)[E], uint32_t T, const int
 }
 
 // Top-k of at most 64 E entries: entry lane + 64 e has score sc[..] and stands
-// for position idx[..] (idx null: itself). False if a tie of keys leaves the
-// set open; else ws.out[0, k) holds the positions in entry order.
+// for position idx[..] (idx null: itself; ascending). ws.out[0, k) holds the
+// positions in entry order. Scores that tie with the k-th best go by position.
+// False, and nothing done, if scores that differ share its key.
 template <int E>
 __device__ inline bool top_k_keys(const double* sc, const int* idx, int n, int k, int lane, TopKScratch& ws) {
   double v[E];
@@ -318,7 +328,27 @@ __device__ inline bool top_k_keys(const double* sc, const int* idx, int n, int k
 #pragma unroll
   for (int e = 0; e < E; ++e) key[e] = lane + 64 * e < n ? score_key(v[e]) : 0u;
   uint32_t T;
-  if (!kth_key<E>(key, k, T)) return false;
+  if (__builtin_expect(!kth_key<E>(key, k, T), 0)) {
+    int above = 0;
+    double tv = 0.0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      above += __popcll(__ballot(key[e] > T));
+      const uint64_t m = __ballot(key[e] == T);
+      if (m) tv = readlane_d(v[e], __builtin_ctzll(m));
+    }
+    bool same = true;
+#pragma unroll
+    for (int e = 0; e < E; ++e) same &= __ballot(key[e] == T && v[e] != tv) == 0;
+    if (!same) return false;
+    int left = k - above;  // the first `left` of the ties: the others leave the set
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const uint64_t m = __ballot(key[e] == T);
+      if (key[e] == T && lanes_below(m) >= left) key[e] = 0u;
+      left -= __popcll(m);
+    }
+  }
   take_keys<E>(key, T, pos, ws.out);
   __builtin_amdgcn_wave_barrier();
   return true;
@@ -333,8 +363,9 @@ __device__ inline bool top_k_keys(const double* sc, const int* idx, int n, int k
 // entries at or above it gives it. Up to 256 entries sit in registers (four a
 // lane) and the threshold is found on their 32-bit keys by ballots. More
 // entries are first cut to those at or above the k-th largest of the 64 lane
-// maxima (k lane maxima reach it, so every top-k entry does). Where keys tie
-// at the boundary the exact ranking decides. (One decode step at 131K: 16 of
+// maxima (k lane maxima reach it, so every top-k entry does). Scores that are
+// equal at the boundary go by position; where scores that differ share a key
+// there, the exact ranking decides. (One decode step at 131K: 16 of
 // 2,027 chunk scores and 32 of 128 group scores took 15.2 + 8.7 and 9.8 thousand
 // cycles with ranks counted in LDS, 7.5 + 4 and 3.7 so. Two bits of the key per
 // step were no faster.)
@@ -358,30 +389,56 @@ __device__ __attribute__((always_inline)) inline int wave_top_k(const double* sc
       for (int u = 0; u < 4; ++u) best[0] = max(best[0], i0 + 64 * u < n ? score_key(v[u]) : 0u);
     }
     uint32_t T;
-    kth_key<1>(best, k_eff, T);
-    int L = 0;
-    for (int j0 = 0; j0 < n; j0 += 256) {
-      double v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = sc[min(j0 + 64 * u + lane, n - 1)];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int p = j0 + 64 * u + lane;
-        const bool q = (p < n) & (score_key(v[u]) >= T);
-        const uint64_t m = __ballot(q);
-        const int pos = L + lanes_below(m);
-        if (q && pos < kListCap) {
-          ws.lv[pos] = v[u];
-          ws.li[pos] = p;
-        }
-        L += __popcll(m);
-      }
+    bool tied = !kth_key<1>(best, k_eff, T);
+    // with all 64 maxima wanted there is no next one to stop T near the k-th
+    // best: it stops at 0 or below, with half the list or more above it
+    if (k_eff == 64) {
+      T = wave_min_u32(best[0]);
+      tied = __popcll(__ballot(best[0] == T)) > 1;
     }
+    // the entries at or above T to the list, in order; FEW: of the ties at T,
+    // which must be equal, the first k
+    double tv = 0.0;
+    int n_ties = 0;
+    bool mixed = false;
+    auto cut = [&](auto few) __attribute__((always_inline)) {
+      constexpr bool FEW = decltype(few)::value;
+      int L = 0;
+      for (int j0 = 0; j0 < n; j0 += 256) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = sc[min(j0 + 64 * u + lane, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int p = j0 + 64 * u + lane;
+          bool q = (p < n) & (score_key(v[u]) >= T);
+          if constexpr (FEW) {
+            const bool tie = q & (score_key(v[u]) == T);
+            const uint64_t m = __ballot(tie);
+            if (m && n_ties == 0) tv = readlane_d(v[u], __builtin_ctzll(m));
+            mixed |= __ballot(tie && v[u] != tv) != 0;
+            q &= !tie | (n_ties + lanes_below(m) < k_eff);
+            n_ties += __popcll(m);
+          }
+          const uint64_t m = __ballot(q);
+          const int pos = L + lanes_below(m);
+          if (q && pos < kListCap) {
+            ws.lv[pos] = v[u];
+            ws.li[pos] = p;
+          }
+          L += __popcll(m);
+        }
+      }
+      return L;
+    };
+    const int L = __builtin_expect(tied, 0) ? cut(std::true_type{}) : cut(std::false_type{});
+    if (__builtin_expect(mixed, 0)) return wave_top_k_ranked(sc, n, k, lane, ws);
+    if (__builtin_expect(L > kListCap, 0)) return top_k_tournament(sc, n, k_eff, lane);
     __builtin_amdgcn_wave_barrier();
     if (L <= 64) done = top_k_keys<1>(ws.lv, ws.li, L, k_eff, lane, ws);
-    else if (L <= kListCap) done = top_k_keys<4>(ws.lv, ws.li, L, k_eff, lane, ws);
+    else done = top_k_keys<4>(ws.lv, ws.li, L, k_eff, lane, ws);
   }
-  if (!done) return wave_top_k_ranked(sc, n, k, lane, ws);
+  if (__builtin_expect(!done, 0)) return wave_top_k_ranked(sc, n, k, lane, ws);
   return lane < k_eff ? ws.out[lane] : kNoIdx;
 }
 

@@ -4,6 +4,8 @@ waves; with a quarter of the chunks bit-identical copies of others, so that
 ties at the boundary are decided by the index. Exact equality with the oracle,
 near-ties included."""
 
+from dataclasses import replace
+
 import pytest
 import torch
 
@@ -25,10 +27,11 @@ def _wl(cands, n_q, first, **kw):
                           grad_begin=0, key_offset="normal", tie_copies=min(cands // 4, (cands - 7) // 2, 300), **kw)
 
 
-def _check(wl, rows):
+def _check(wl, rows, Kn=None, Qn=None):
     hc, cfg = P.hcfg_of(wl), P.cfg_of(wl)
     end = wl.q_begin + wl.n_q
-    Kn, Qn = synth.keys(wl, 0, end), synth.queries(wl, wl.q_begin, end)
+    if Kn is None:
+        Kn, Qn = synth.keys(wl, 0, end), synth.queries(wl, wl.q_begin, end)
     K, Q = P.to_dev(Kn), P.to_dev(Qn)
     cs, gs = hga.alloc_summaries(hc, -(-end // 64) * 64)
     hga.build_summaries(hc, K, 0, end, cs, gs)
@@ -65,3 +68,32 @@ def test_rows_four_per_workgroup(cands):
 def test_blocks(cands, n_q, n_kv):
     """Block routing with one and with several blocks per workgroup."""
     _check(_wl(cands, n_q, 0, n_kv_heads=n_kv, n_q_heads=2 * n_kv), False)
+
+
+@pytest.mark.parametrize("cands", [257, 700, 4200])
+def test_rows_one_per_workgroup(cands):
+    """More (row, kv head) pairs than CUs, but too few rows for four per
+    workgroup: one to two passes of 256 candidates, and two rounds of 4,096."""
+    _check(_wl(cands, 40, 20, n_kv_heads=8, n_q_heads=8), True)
+
+
+@pytest.mark.parametrize("kc,kg", [(8, 16), (16, 64), (64, 16), (64, 64)])
+@pytest.mark.parametrize("steps", [1, 32])
+@pytest.mark.parametrize("cands,n_q,rows", [(60, 1, True), (250, 40, True), (700, 1, True), (700, 600, True),
+                                            (60, 64, False), (250, 64, False), (700, 64, False), (700, 8448, False)])
+def test_equal_scores_and_shared_keys(cands, n_q, rows, steps, kc, kg):
+    """Scores that are all equal (steps 1: the selection goes by position
+    alone) and scores of 32 values 2^-20 apart at 256, which all round to one
+    float: the routing's 32-bit keys cannot tell them apart."""
+    wl = replace(_wl(cands, n_q, 0, top_chunks=kc, top_groups=kg), tie_copies=0)
+    end, g = wl.q_begin + wl.n_q, wl.group_size
+    tok = torch.arange(end)
+    K = torch.zeros(end, 2, 64)
+    K[:, :, 0] = 256.0
+    K[:, 0, 1] = (tok // 64 * 7 % 32 % steps).float() * 2.0 ** -20
+    K[:, 1, 1] = (tok // 64 * 13 % 32 % steps).float() * 2.0 ** -20
+    K[:, :, 2] = ((tok // g * 5 % 8 % steps).float() * 2.0 ** -24)[:, None]
+    Q = torch.zeros(wl.n_q, 4, 64)
+    Q[:, :, :3] = 1.0
+    K, Q = (x.to(torch.bfloat16).view(torch.int16).numpy().view("uint16") for x in (K, Q))
+    _check(wl, rows, K, Q)
