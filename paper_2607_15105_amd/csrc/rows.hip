@@ -102,7 +102,7 @@ struct RowsRoute {
   static constexpr int RR = RB == 1 ? kRowsRouteRound : 512;
 };
 
-// NT threads: 256, or 1,024 for one row with more than 256 candidates. There
+// NT threads: 256, or 1,024 for one row with more than 512 candidates. There
 // the sixteen waves score 1,024 candidates a pass and each selects from a
 // sixteenth of the round (contiguous, so that kept positions stay in chunk
 // order); wave 0 then selects from the kept entries of all. (Decode step at
@@ -264,6 +264,12 @@ route_rows_kernel(RouteArgs a, int64_t n_rows, int stride) {
   }
 }
 
+// Candidates of a row from which on sixteen waves route it: four waves take
+// 256 a pass, and the merging of sixteen selections costs about a pass (Qwen3-8B
+// layer, one row, k_c 8: 286 to 478 candidates 12.3-13.7 us with four waves and
+// 15.1-16.1 with sixteen, 542 to 766 15.4 and 15.4, 1,022 17.7 and 15.6).
+constexpr int kRowsRouteWide = 512;
+
 // Rows per routing workgroup: four when the call still fills the chip with
 // (four rows, kv head) workgroups (each summary row read then serves four
 // rows), else one (decode steps and short calls keep one workgroup per row).
@@ -290,7 +296,7 @@ hipError_t launch_route_rows(const RouteArgs& a, int64_t n_rows, int n_cand_max,
   const bool alone = n_rows * a.n_kv_heads <= 256;  // one workgroup per CU at most
   if (rb == 4) HGA_RRT(4, 256, false);
   else if (!alone) HGA_RRT(1, 256, false);
-  else if (n_cand_max > 256) HGA_RRT(1, 1024, false);
+  else if (n_cand_max > kRowsRouteWide) HGA_RRT(1, 1024, false);
   else HGA_RRT(1, 256, true);
 #undef HGA_RRT
 #undef HGA_RR

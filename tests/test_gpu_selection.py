@@ -52,9 +52,9 @@ def _check(wl, rows, Kn=None, Qn=None):
 
 
 @pytest.mark.parametrize("kc,kg", [(8, 16), (16, 64), (64, 13)])
-@pytest.mark.parametrize("cands", [9, 64, 65, 256, 257, 289, 700])
+@pytest.mark.parametrize("cands", [9, 64, 65, 256, 257, 289, 512, 513, 700])
 def test_one_row(cands, kc, kg):
-    """A decode step: four waves up to 256 candidates, sixteen beyond."""
+    """A decode step: four waves up to 512 candidates, sixteen beyond."""
     _check(_wl(cands, 1, 37, top_chunks=kc, top_groups=kg), True)
 
 
