@@ -325,7 +325,7 @@ hga_status_t hga_route_rows(const hga_config_t* cfg, const void* Q, hga_strides_
  *              its rounding to cfg->dtype, for hga_attend_rows_bwd.
  * Scores, softmax and accumulation in float32. With bf16 inputs P enters P.V
  * as a pair of bf16 values (hi + lo, to about 2^-17), whether o_f32 is given or
- * not; with float32 inputs it is not rounded. Three forms of the kernel share
+ * not; with float32 inputs it is not rounded. Several forms of the kernel serve
  * calls of few, more and many rows, so a row's result can differ in its last
  * float32 bits (O before its rounding) with the number of rows in the call.
  */

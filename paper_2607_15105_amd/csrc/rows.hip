@@ -541,19 +541,48 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
 // are in LDS (one buffer per wave, K and then V).
 //
 // KW == 1: a wave per group, four groups per workgroup. KW > 1 (few rows):
-// the KW waves of a workgroup take every KW-th step of one group's lists and
-// merge their softmax states through LDS.
+// the KW waves of a workgroup take every KW-th step of one group's lists (of one
+// row's, where RPW == 1) and merge their softmax states through LDS.
 //
 // Strictly causal 1,024-row segment at 16K (Qwen3-8B layer): 172 us with one
 // workgroup per row and one lane per key, 50 us so; a decode step at 16K 9.6 and
 // 7.1 us.
 constexpr int kRowsStep = 32;  // keys of a step
-// Which form a call takes, by its (group, kv head) and (row, kv head) pairs.
-// Qwen3-8B layer, 320 keys a row: 256 rows (512 group pairs) take 27.8 us with
-// a wave per group and 19.2 with four, 512 rows 29.9 and 33.7, 1,024 rows 50
-// and 61; 32 rows (256 pairs) take 12.3 us with four waves per group of rows
-// and 8.2 with twelve per row, 64 rows 12.7 and 14.7.
-constexpr int64_t kRowsWaveGroups = 1024, kRowsSplitPairs = 512;
+// Which form a call takes. A wave per group from 1,024 (group, kv head) pairs on
+// (Qwen3-8B layer, 320 keys a row: 256 rows, 512 group pairs, take 27.8 us so and
+// 19.2 with four waves, 512 rows 29.9 and 33.7, 1,024 rows 50 and 61); below,
+// rows on their own while they are few, else four waves per group.
+constexpr int64_t kRowsWaveGroups = 1024;
+
+// The keys of the last row's block in the windows, and those of a row's
+// selected groups, at most.
+static int64_t window_keys(const AttnArgs& a, int64_t n_rows) {
+  const int64_t end = ((a.q_begin + n_rows - 1) / 64 + 1) * 64;
+  const int64_t ls = end > a.local_tokens ? end - a.local_tokens : 0;
+  return (a.sink_tokens < ls ? a.sink_tokens : ls) + end - ls;
+}
+static int64_t private_keys(const AttnArgs& a) { return (int64_t)a.top_groups << a.group_shift; }
+
+// Rows on their own, or in groups of `rpw` that share the windows' keys: up to
+// 256 (row, kv head) pairs, one workgroup per CU, always on their own; up to
+// `most` pairs where the windows do not outweigh what the rows have for
+// themselves. Two rows' workgroups share a CU then and take about 1.5 (windows +
+// private) keys' time, a group windows + rpw private. (Forward, Qwen3-8B layer,
+// own rows and groups, us: 512 pairs, windows 192 and private 128 keys 10.5 and
+// 13.4, 192 and 1,024 25 and 53, 8,320 and 128 123 and 86; 640 pairs 13.5 and
+// 13.8, 800 16.3 and 14.0. Eight heads a row, groups of two, 512 pairs: 192 and
+// 128 11.2 and 10.8, 192 and 1,024 26 and 32.)
+static bool rows_apart(const AttnArgs& a, int64_t n_rows, int rpw, int64_t most) {
+  const int64_t pairs = n_rows * a.n_kv_heads;
+  return pairs <= 256 || (pairs <= most && window_keys(a, n_rows) < (2 * rpw - 3) * private_keys(a));
+}
+
+// Waves for a row on its own: four, or `many` where it has a CU to itself and
+// more than `steps` steps to walk (one row, forward: 320 keys 7.5 us with four
+// and 8.0 with twelve, 576 9.8 and 10.0, 704 11.0 and 11.0, 1,216 15.9 and 13.7).
+static bool many_waves(const AttnArgs& a, int64_t n_rows, int64_t steps) {
+  return n_rows * a.n_kv_heads <= 256 && window_keys(a, n_rows) + private_keys(a) > steps * kRowsStep;
+}
 
 // Maximum and sum over the four lanes l % 16 + 16 i, the same in each.
 __device__ inline float quad_max(float x) {
@@ -707,15 +736,18 @@ struct RowRegs {
 };
 
 template <int D, int G, int RPW, int KW>
-__global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void attend_rows_fwd_mfma_kernel(AttnArgs a, int64_t n_rows,
-                                                                                      int64_t n_groups) {
+__global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void
+attend_rows_fwd_mfma_kernel(AttnArgs a, int64_t n_rows, int64_t n_groups) {
   constexpr int NS = D / 32;       // k steps of S
   constexpr int NT = D / 16;       // 16-row tiles of O^T
   constexpr int KP = D * 2 + 16;   // LDS pitch of a K row: an operand read's sixteen rows start 4 banks apart
   constexpr int VP = D * 2 + 32;   // and of a V row: a transpose load's eight rows start 8 banks apart
   constexpr int NW = KW == 1 ? 4 : KW;
   constexpr int NG = KW == 1 ? 4 : 1;  // groups per workgroup
-  constexpr int NV = 4;  // V tiles at a time: a tile's two products are not one after the other
+  // V tiles at a time, so that a tile's two products are not one after the
+  // other (d = 64: two keep it at four waves per SIMD; four took 52 us where
+  // two take 44, 2,048 rows)
+  constexpr int NV = D / 32;
   static_assert(RPW * G <= 16, "a group's pairs are the columns of one product");
   // each wave's K, then V rows of its current step; with KW > 1, at the end, its O
   __shared__ __attribute__((aligned(16))) char s_v[NW][kRowsStep * VP];
@@ -970,12 +1002,15 @@ hipError_t rows_fwd_mfma(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
   if (ng * a.n_kv_heads >= kRowsWaveGroups) {
     hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, R, 1>), dim3((unsigned)((ng + 3) / 4 * a.n_kv_heads)),
                        dim3(256), 0, s, a, n_rows, ng);
-  } else if (n_rows * a.n_kv_heads >= kRowsSplitPairs) {
+  } else if (!rows_apart(a, n_rows, R, 640)) {
     hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, R, 4>), dim3((unsigned)(ng * a.n_kv_heads)), dim3(256), 0,
                        s, a, n_rows, ng);
-  } else {
+  } else if (many_waves(a, n_rows, 24)) {
     hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, 1, 12>), dim3((unsigned)(n_rows * a.n_kv_heads)),
                        dim3(768), 0, s, a, n_rows, n_rows);
+  } else {
+    hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, 1, 4>), dim3((unsigned)(n_rows * a.n_kv_heads)),
+                       dim3(256), 0, s, a, n_rows, n_rows);
   }
   return hipGetLastError();
 }

@@ -1,6 +1,6 @@
 """Per-query attention on groups of rows (hga_attend_rows_fwd, bf16): the
-three forms a call can take (a wave per group, four waves per group, twelve
-waves per row), with partial first and last groups, for every head ratio; and
+four forms a call can take (a wave per group, four waves per group, four or
+twelve waves per row), with partial first and last groups, for every head ratio; and
 what a row does not attend stays out of its result, infinities and NaN too,
 although the rows of a group share products."""
 
@@ -16,9 +16,10 @@ from tests.test_gpu_rows import _gpu, _rows_bwd_check, _rows_check  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-# (row, kv head) pairs below 512: twelve waves per row; above, four waves per
-# group, and from 1,024 (group, kv head) pairs a wave per group
-@pytest.mark.parametrize("n_q,q_begin", [(1, 1787), (63, 1500), (66, 1537), (515, 1501)])
+# 232 keys a row: four waves per row up to 640 (row, kv head) pairs (256 with
+# eight heads), then four waves per group, and from 1,024 (group, kv head) pairs
+# a wave per group
+@pytest.mark.parametrize("n_q,q_begin", [(1, 1787), (63, 1500), (66, 1537), (99, 1501), (515, 1501)])
 @pytest.mark.parametrize("G,d", [(1, 64), (2, 64), (4, 128), (8, 64)])
 def test_rows_forms(G, d, n_q, q_begin):
     wl = synth.Workload("rows_forms", T=2048, n_q_heads=8 * G, n_kv_heads=8, head_dim=d, dtype="bf16", seed=31,
@@ -73,7 +74,7 @@ def test_rows_not_attending_a_non_finite_value_keep_their_result(n_q, bad):
     assert (lse - lse2).abs().max() <= 1e-5
 
 
-# four waves per group of rows below 1,024 (group, kv head) pairs, then one
+# dQ: four waves per row up to 512 pairs, four per group, a wave per group
 @pytest.mark.parametrize("n_q,q_begin", [(3, 1665), (66, 1537), (515, 1501)])
 @pytest.mark.parametrize("G,d", [(1, 64), (2, 64), (4, 128), (8, 64)])
 def test_rows_backward_forms(G, d, n_q, q_begin):
@@ -83,7 +84,7 @@ def test_rows_backward_forms(G, d, n_q, q_begin):
     _rows_bwd_check(wl, repeat=True)
 
 
-@pytest.mark.parametrize("n_q", [12, 600])
+@pytest.mark.parametrize("n_q", [12, 130, 600])
 def test_rows_dq_of_rows_not_attending_a_non_finite_key(n_q):
     """An infinity in the K row of a token of the call and of a token that
     some rows select: dQ of the rows that attend neither stays what it is,
@@ -125,7 +126,7 @@ def test_rows_dq_of_rows_not_attending_a_non_finite_key(n_q):
     assert (dq(K, None) - dq(K, o32)).abs().max() <= 2e-2
 
 
-# the three forms, by rows: twelve waves per row, four waves per group, a wave per group
+# three of the forms, by rows: four waves per row, four per group, a wave per group
 @pytest.mark.parametrize("tails", [False, True])
 @pytest.mark.parametrize("n_q", [20, 90, 600])
 def test_rows_float32_output_keeps_the_weights(n_q, tails):
@@ -161,3 +162,14 @@ def test_rows_float32_output_keeps_the_weights(n_q, tails):
         worst = max(worst, float((o32[:, 4 * h:4 * h + 4] - want).norm() / want.norm()))
         assert (lse[:, 4 * h:4 * h + 4] - torch.logsumexp(s, -1)).abs().max() <= 3e-6
     assert worst <= 1e-5
+
+
+@pytest.mark.parametrize("n_q,q_begin", [(1, 1787), (33, 1503)])
+@pytest.mark.parametrize("G,d", [(1, 128), (4, 64), (4, 128), (8, 128)])
+def test_rows_long_lists(G, d, n_q, q_begin):
+    """More than 24 steps of 32 keys a row, few rows: twelve waves per row, and
+    eight for dQ up to 256 pairs; with 264 pairs four."""
+    wl = synth.Workload("rows_long", T=2048, n_q_heads=8 * G, n_kv_heads=8, head_dim=d, dtype="bf16", seed=37,
+                        q_begin=q_begin, n_q=n_q, grad_begin=q_begin // 64 * 64 - 64, key_offset="normal",
+                        group_size=16, top_chunks=16, top_groups=64, local_tokens=64)
+    _rows_bwd_check(wl, repeat=True)
