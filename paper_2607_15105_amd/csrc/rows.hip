@@ -571,7 +571,8 @@ static int64_t private_keys(const AttnArgs& a) { return (int64_t)a.top_groups <<
 // own rows and groups, us: 512 pairs, windows 192 and private 128 keys 10.5 and
 // 13.4, 192 and 1,024 25 and 53, 8,320 and 128 123 and 86; 640 pairs 13.5 and
 // 13.8, 800 16.3 and 14.0. Eight heads a row, groups of two, 512 pairs: 192 and
-// 128 11.2 and 10.8, 192 and 1,024 26 and 32.)
+// 128 11.2 and 10.8, 192 and 1,024 26 and 32. dQ: 512 pairs 23.2 and 24.6, 39.6
+// and 60, 149 and 97; 640 pairs 30 and 26.)
 static bool rows_apart(const AttnArgs& a, int64_t n_rows, int rpw, int64_t most) {
   const int64_t pairs = n_rows * a.n_kv_heads;
   return pairs <= 256 || (pairs <= most && window_keys(a, n_rows) < (2 * rpw - 3) * private_keys(a));
@@ -579,7 +580,9 @@ static bool rows_apart(const AttnArgs& a, int64_t n_rows, int rpw, int64_t most)
 
 // Waves for a row on its own: four, or `many` where it has a CU to itself and
 // more than `steps` steps to walk (one row, forward: 320 keys 7.5 us with four
-// and 8.0 with twelve, 576 9.8 and 10.0, 704 11.0 and 11.0, 1,216 15.9 and 13.7).
+// and 8.0 with twelve, 576 9.8 and 10.0, 704 11.0 and 11.0, 1,216 15.9 and 13.7;
+// dQ: 320 keys 13.8 with four and 14.3 with eight, 576 16.1 and 15.9, 1,216 22.7
+// and 20.8).
 static bool many_waves(const AttnArgs& a, int64_t n_rows, int64_t steps) {
   return n_rows * a.n_kv_heads <= 256 && window_keys(a, n_rows) + private_keys(a) > steps * kRowsStep;
 }
@@ -1242,19 +1245,19 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
 // workgroup per row, one lane per key) + 8.8 us (D, a kernel of its own)
 // before, 57 us in all so.
 template <int D, int G, int RPW, int KW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void rows_dq_mfma_kernel(AttnArgs a,
+__global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void rows_dq_mfma_kernel(AttnArgs a,
                                                                                      int64_t n_rows, int64_t n_groups) {
   using TL = Tile<__bf16, D>;
   constexpr int NS = D / 32;       // k steps of S and dP
   constexpr int NT = D / 16;       // 16-row tiles of dQ^T
   constexpr int TB = kRowsStep * TL::kRowPitch;  // bytes of 32 rows
+  constexpr int NW = KW == 1 ? 4 : KW;
   constexpr int NG = KW == 1 ? 4 : 1;            // groups per workgroup
   static_assert(RPW * G <= 16, "a group's pairs are the columns of one product");
-  static_assert(KW == 1 || KW == 4, "four waves");
   // each wave's K and V rows of its current step; with KW > 1, at the end, its dQ
-  __shared__ __attribute__((aligned(16))) char s_kv[4][2 * TB];
-  __shared__ int s_sel[4][RPW * 64];
-  __shared__ int s_bad[4];
+  __shared__ __attribute__((aligned(16))) char s_kv[NW][2 * TB];
+  __shared__ int s_sel[NW][RPW * 64];
+  __shared__ int s_bad[NW];
   static_assert(16 * D * 4 <= 2 * TB, "a wave's partial dQ fits its buffer");
   typedef __attribute__((address_space(3))) s16x4* lds_s4;
   prefetch_args(a);
@@ -1847,12 +1850,17 @@ hipError_t rows_bwd_g(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
   if constexpr (Elem<T>::kBytes == 2) {
     constexpr int R = rows_per_group<G>();
     const int64_t ng = n_row_groups(a, n_rows, R);
+    const dim3 each((unsigned)(n_rows * a.n_kv_heads));
     if (ng * a.n_kv_heads >= kRowsWaveGroups)
       hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 1>), dim3((unsigned)((ng + 3) / 4 * a.n_kv_heads)), dim3(256),
                          0, s, a, n_rows, ng);
-    else
+    else if (!rows_apart(a, n_rows, R, 512))
       hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 4>), dim3((unsigned)(ng * a.n_kv_heads)), dim3(256), 0, s, a,
                          n_rows, ng);
+    else if (many_waves(a, n_rows, 16))
+      hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, 1, 8>), each, dim3(512), 0, s, a, n_rows, n_rows);
+    else
+      hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, 1, 4>), each, dim3(256), 0, s, a, n_rows, n_rows);
   } else {
     const int64_t pairs = n_rows * a.n_q_heads;
     hipLaunchKernelGGL((rows_rowdot_kernel<T, D>), dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, s, a, n_rows);
