@@ -252,9 +252,9 @@ hga_status_t hga_attend_gathered_fwd(const hga_config_t* cfg, const void* Q, hga
  *              * (q_begin + n_q - grad_begin) * Hkv * d floats: most routed
  *              keys then lie in the active segment and the dK/dV work of
  *              each chunk is split over those subsets. p is 2, or 4 or 8 for
- *              calls of few rows and heads; it depends on the heads, q_begin,
- *              n_q and grad_begin, so a shorter call's size may be the
- *              larger. A buffer that holds fewer subsets, down to two, is
+ *              calls of few rows and heads; it depends on the configuration,
+ *              q_begin, n_q and grad_begin, so a shorter call's size may be
+ *              the larger. A buffer that holds fewer subsets, down to two, is
  *              taken too (one sized for a longer call of the same q_begin
  *              and grad_begin always is): the call then splits into as many
  *              as fit. Its contents need no initialisation.

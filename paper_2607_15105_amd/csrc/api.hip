@@ -91,16 +91,20 @@ size_t route_ws(const hga_config_t* c, int64_t n_q) {
 // second kernel sums. (1,024-token segments of the 16K step: two subsets
 // win below 6 k_c history chunks, one above; four never won.)
 //
-// Such a call with few heads or few rows is split further, up to one query head
-// per item, while its dK/dV and dQ workgroups still run at once (one per CU):
-// its time is the longest item's chain of (block, query head) steps. Past 256
-// workgroups a second round costs more than a short chain saves, so only
-// chains of 32 steps and more go there. Two subsets against four: float32,
-// 1,024 rows, 8/2 heads 194 and 107 us; bf16, 1,024 rows, 8/2 heads 60 and 38;
-// 16/4 heads (320 workgroups, 32 steps) 63 and 50; 512 rows, 32/8 heads (320
-// workgroups, 16 steps) 40 and 47. With much history the items are short and
-// the combining pass costs more than a split saves (512 rows at 15,360, 32/8
-// heads: 31 us in one item, 44 in two).
+// Such a call is split further, up to one query head per item, while its dK/dV
+// and dQ workgroups still run at once (one per CU) and the longest dK/dV chain
+// of (block, query head) steps is what the others wait for: a further split
+// halves it, but not below the dQ items' time, and costs the writing and
+// combining of twice the partials. In steps (1.36 us for bf16 at d = 128, 1.1 at
+// 64, 5.5 for float32): a chain is the blocks that attend the most attended
+// chunk (all of them where the sink window is active, else the window's and,
+// of the others, 1.25 times a candidate chunk's mean share) times the heads of
+// an item; a dQ item takes 2 steps per 64 routed keys (1.5 for bf16 at d = 64);
+// the further partials 1 us + 0.8 us per MB. Past 256 workgroups dQ waits for a
+// first dK/dV item to end: worth 14 steps. (Over 618 calls of 64 to 2,048 rows,
+// 4 to 8 heads per kv head, against two subsets: 6 slower, by 9% at most, the
+// float32 call of 1,024 rows and 8/2 heads 195 -> 107 us, bf16 with 8/1 heads
+// 81 -> 31. A split by workgroups alone was slower in 287, up to 1.37 times.)
 int bwd_parts(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_begin) {
   const int G = c->n_q_heads / c->n_kv_heads;
   if (c->bwd_kv_parts == 1) return 1;
@@ -110,14 +114,37 @@ int bwd_parts(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_
   const int64_t h0 = ls > 0 && ls / kChunk > first ? ls / kChunk - first : 0;  // history candidates
   const int64_t kc = c->top_chunks > 0 ? c->top_chunks : 1;
   if (h0 >= 6 * kc || G < 2) return 1;
-  const int64_t n_qb = n_q / kChunk;
-  const int64_t n_kv = (q_begin + n_q - grad_begin) / kChunk * c->n_kv_heads;
+  const int64_t n_qb = n_q / kChunk, q_end = q_begin + n_q;
+  const int64_t n_kv = (q_end - grad_begin) / kChunk * c->n_kv_heads;
   const int64_t n_dq = n_qb * c->n_kv_heads * (G > 4 ? G / 4 : 1);
+  auto cands = [&](int64_t end) {  // candidate chunks of the block that ends at `end`
+    const int64_t l = end - c->local_tokens;
+    return l > 0 && l / kChunk > first ? l / kChunk - first : 0;
+  };
+  // routed keys of the last block
+  const int64_t last_ls = q_end > c->local_tokens ? q_end - c->local_tokens : 0;
+  const int64_t chosen = c->top_chunks < cands(q_end) ? c->top_chunks : cands(q_end);
+  const int64_t groups = chosen * (kChunk / c->group_size);
+  const int64_t keys = (c->sink_tokens < last_ls ? c->sink_tokens : last_ls) + q_end - last_ls +
+                       (c->top_groups < groups ? c->top_groups : groups) * c->group_size;
+  const bool bf16 = c->dtype == HGA_BF16, narrow = bf16 && c->head_dim == 64;
+  const double step_us = !bf16 ? 5.5 : narrow ? 1.1 : 1.36;
+  const double dq = (narrow ? 1.5 : 2.0) * (double)((keys + 63) / 64);
+  double visits = (double)n_qb;  // blocks that attend the most attended chunk
+  if (grad_begin >= c->sink_tokens) {
+    const double near = (double)c->local_tokens / kChunk;
+    const int64_t mid = cands(q_begin + n_q / 2);
+    const double share = 1.25 * (double)c->top_chunks / (double)(mid > 0 ? mid : 1);
+    if (near < visits) visits = near + (visits - near) * (share < 1.0 ? share : 1.0);
+  }
   int p = 2;
-  while (p < G) {
+  for (; p < G; p *= 2) {
     const int64_t wgs = 2 * p * n_kv + n_dq;
-    if (wgs > 320 || (wgs > 256 && n_qb * (G / p) < 32)) break;
-    p *= 2;
+    if (wgs > 320) break;
+    const double chain = visits * G / p;
+    const double gain = (chain > dq ? chain : dq) - (chain / 2 > dq ? chain / 2 : dq);
+    const double mb = 2e-6 * p * (double)(q_end - grad_begin) * c->n_kv_heads * c->head_dim * sizeof(float);
+    if (gain * step_us < 1.0 + 0.8 * mb || (wgs > 256 && gain < 14.0)) break;
   }
   return p;
 }
@@ -138,8 +165,8 @@ size_t bwd_ws(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_
 // The split of a call with `bytes` of workspace: the one above, or, where that
 // does not fit, the finest that does; 0 if not even two subsets do (one, where
 // the call does not split). The finer splits belong to short calls, so a short
-// call can want more than a longer one (32/8 heads, d = 128: 256 rows 8.4 MB,
-// 448 rows 7.4 MB), and a buffer sized for the longer one has to do for both.
+// call can want more than a longer one (8/1 heads, d = 64: 2,048 rows 8.5 MB,
+// 4,032 rows 4.3 MB), and a buffer sized for the longer one has to do for both.
 int bwd_parts_in(const hga_config_t* c, int64_t q_begin, int64_t n_q, int64_t grad_begin, size_t bytes) {
   int p = bwd_parts(c, q_begin, n_q, grad_begin);
   while (p > 2 && bwd_ws_of(c, q_begin, n_q, grad_begin, p) > bytes) p /= 2;

@@ -33,6 +33,9 @@ def _parts(wl):
     (2, 2, 256, 128, 128, "bf16", 2),
     (1, 4, 256, 0, 64, "bf16", 1),
     (4, 2, 256, 4096, 64, "bf16", 1),   # history
+    (4, 8, 256, 0, 128, "bf16", 2),     # dQ is as long as the chains
+    (4, 4, 1024, 2048, 128, "bf16", 2),  # the sink chunk is not active: short chains, 320 workgroups
+    (8, 1, 1024, 512, 64, "bf16", 8),   # nor here, but every block picks the few candidates
 ])
 def test_library_choice(G, n_kv, n_q, q_begin, d, dtype, parts):
     if not torch.cuda.is_available():
@@ -43,27 +46,27 @@ def test_library_choice(G, n_kv, n_q, q_begin, d, dtype, parts):
 
 
 def test_a_buffer_sized_for_a_longer_call_takes_a_shorter_one():
-    """32/8 heads from token 0: 256 rows split into four subsets and 448 rows
-    into two, in fewer bytes. In the longer call's buffer the shorter call
-    splits into two, as where the caller asks for two."""
+    """8/1 heads from token 0: 2,048 rows split into eight subsets and 4,032
+    rows into two, in half the bytes. In the longer call's buffer the shorter
+    call splits into two, as where the caller asks for two."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
-    wl = _wl(4, 8, 256, 0, 128, "bf16")
+    wl = _wl(8, 1, 2048, 0, 64, "bf16")
     hc = P.hcfg_of(wl)
-    two = hga.make_config(32, 8, 128, group_size=wl.group_size, top_chunks=wl.top_chunks, top_groups=wl.top_groups,
+    two = hga.make_config(8, 1, 64, group_size=wl.group_size, top_chunks=wl.top_chunks, top_groups=wl.top_groups,
                           sink_tokens=wl.sink_tokens, local_tokens=wl.local_tokens, bwd_kv_parts=2)
-    small, full = (hga.workspace_size(hc, hga.OP_BWD, 0, n, 0) for n in (448, 256))
-    assert hga.workspace_size(two, hga.OP_BWD, 0, 256, 0) < small < full
-    K, V, Q, dO = (P.to_dev(f(wl, 0, 256)) for f in (synth.keys, synth.values, synth.queries, synth.grad_output))
-    cs, gs = hga.alloc_summaries(hc, 256)
-    rb = hga.alloc_route(hc, 0, 256)
-    O, lse = torch.empty_like(Q), torch.empty(256, 32, device="cuda")
-    hga.build_summaries(hc, K, 0, 256, cs, gs)
+    small, full = (hga.workspace_size(hc, hga.OP_BWD, 0, n, 0) for n in (4032, 2048))
+    assert hga.workspace_size(two, hga.OP_BWD, 0, 2048, 0) < small < full
+    K, V, Q, dO = (P.to_dev(f(wl, 0, 2048)) for f in (synth.keys, synth.values, synth.queries, synth.grad_output))
+    cs, gs = hga.alloc_summaries(hc, 2048)
+    rb = hga.alloc_route(hc, 0, 2048)
+    O, lse = torch.empty_like(Q), torch.empty(2048, 8, device="cuda")
+    hga.build_summaries(hc, K, 0, 2048, cs, gs)
     hga.route_attend_fwd(hc, Q, K, V, 0, cs, gs, rb.sel_chunks, rb.sel_groups, rb.n_sel_groups, O, lse, rb.workspace)
 
     def grads(cfg, size):
         ws = torch.full((size + 256,), 0xFF, dtype=torch.uint8, device="cuda")
-        out = [torch.empty(256, h, 128, device="cuda") for h in (32, 8, 8)]
+        out = [torch.empty(2048, h, 64, device="cuda") for h in (8, 1, 1)]
         hga.attend_bwd(cfg, Q, K, V, O, dO, lse, 0, 0, rb.sel_groups, rb.n_sel_groups, *out, ws[:size])
         torch.cuda.synchronize()
         assert bool((ws[size:] == 0xFF).all())  # nothing past the buffer's end
