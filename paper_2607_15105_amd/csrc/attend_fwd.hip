@@ -187,7 +187,7 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
       }
       l_run += psum;
       // O^T += V^T . P^T over this half's keys
-  #pragma unroll
+#pragma unroll
       for (int s2 = 0; s2 < VPS; ++s2) {
         const int s = t * VPS + s2;
         float pv[E], plo[E];
@@ -206,7 +206,7 @@ __device__ __forceinline__ void attend_block(const AttnArgs& a, const WgCoord wc
           if constexpr (PREC) oacc[dt] = EL::mma(vf, EL::frag_from(plo), oacc[dt]);
         }
       }
-      }
+    }
   };
 
   if constexpr (!LATE) {
@@ -369,7 +369,8 @@ constexpr bool three_per_simd() { return Elem<T>::kBytes == 2 && D == 64 && GW =
 // gather and the softmax maximum went through the LDS crossbar, 1,579 us (742
 // TFLOP/s) now.
 template <typename T, int D, int GW, bool PREC, bool CMP>
-__global__ __launch_bounds__(128 * GW) __attribute__((amdgpu_waves_per_eu(three_per_simd<T, D, GW>() ? 3 : 1))) void attend_fwd_kernel(AttnArgs a) {
+__global__ __launch_bounds__(128 * GW) __attribute__((amdgpu_waves_per_eu(three_per_simd<T, D, GW>() ? 3 : 1))) void
+attend_fwd_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[2 * (Tile<T, D>::kRowBytes +
                                                          (Elem<T>::kBytes == 2 ? Tile<T, D>::kRowBytes
                                                                                : Tile<T, D>::kTBytes))];

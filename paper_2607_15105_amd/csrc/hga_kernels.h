@@ -71,7 +71,7 @@ struct AttnArgs {
   int top_groups, group_shift;
   int sink_tokens, local_tokens;
   int n_act_chunks;
-  float* dvec;              // backward: rowsum(dO * O) [n_q][Hq], from the row-dot kernel
+  float* dvec;              // backward: D = rowsum(dO * O) [n_q][Hq], from the row-dot kernel (bf16 rows: from dQ's)
   int kv_parts;             // dK/dV work items per (chunk, kv head): query-head subsets
   float* part_out;          // kv_parts > 1: partial dK then dV, [part][chunk][Hkv][64][D] each
   int64_t r_cap;            // > 0: K/V are compact routed rows [n_qb][Hkv][r_cap][D] (gather / gathered forward)

@@ -305,6 +305,9 @@ hipError_t launch_route_rows(const RouteArgs& a, int64_t n_rows, int n_cand_max,
 
 // ---------------------------------------------------------------- attention
 
+// The float32 kernels are for head dim 64, which is what float32 is built for.
+__device__ inline float load_f32(const char* p) { return *reinterpret_cast<const float*>(p); }
+
 // Wave-wide maximum and sum, the same value in every lane: DPP steps inside
 // each 16-lane row (swap neighbours, swap pairs, mirror each half-row,
 // mirror the row), then the four rows' values read as scalars. No step goes
@@ -364,13 +367,11 @@ __device__ inline RowSet row_set(const AttnArgs& a, int64_t row, int h) {
   return r;
 }
 
-template <typename T, int D, int G>
+template <int G>
 __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
-  constexpr int EB = Elem<T>::kBytes;
-  constexpr int E = D / 64;             // head-dim elements of a lane in P.V
-  constexpr int NP = D * EB / 16;       // 16-byte pieces of a key row
-  constexpr int EP = 16 / EB;           // elements per piece
-  constexpr int VP = D * EB + 16;       // LDS pitch of a staged V row (padded against bank conflicts)
+  constexpr int D = 64;                 // a lane per head-dim element in P.V
+  constexpr int NP = D / 4;             // 16-byte pieces of a key row
+  constexpr int VP = D * 4 + 16;        // LDS pitch of a staged V row (padded against bank conflicts)
   __shared__ __attribute__((aligned(16))) float s_q[G][D];
   __shared__ float s_m[4][G], s_l[4][G];
   __shared__ float s_o[4][G][D];
@@ -385,21 +386,20 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
 
   for (int x = tid; x < G * D; x += 256) {
     const int g = x / D, e = x % D;
-    s_q[g][e] = load_elem<T, D>(Qb + (row * a.q_tok + (int64_t)(h * G + g) * a.q_head + e) * EB);
+    s_q[g][e] = load_f32(Qb + (row * a.q_tok + (int64_t)(h * G + g) * a.q_head + e) * 4);
   }
   const RowSet rs = row_set(a, row, h);
   __syncthreads();
 
-  float m[G], l[G], o[G][E];
+  float m[G], l[G], o[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     m[g] = -__builtin_inff();
     l[g] = 0.0f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) o[g][e] = 0.0f;
+    o[g] = 0.0f;
   }
-  const int64_t k_stride = a.k_tok * EB, v_stride = a.v_tok * EB;
-  const int64_t k_head = (int64_t)h * a.k_head * EB, v_head = (int64_t)h * a.v_head * EB;
+  const int64_t k_stride = a.k_tok * 4, v_stride = a.v_tok * 4;
+  const int64_t k_head = (int64_t)h * a.k_head * 4, v_head = (int64_t)h * a.v_head * 4;
   for (int tb = wave * 64; tb < rs.R; tb += 256) {
     const int p = tb + lane;
     const bool valid = p < rs.R;
@@ -418,22 +418,14 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
     for (int g = 0; g < G; ++g) s[g] = 0.0f;
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
-      float kx[EP];
-#pragma unroll
-      for (int e = 0; e < EP; ++e) {
-        if constexpr (EB == 2) kx[e] = bf16_bits_to_float((kw[c][e >> 1] >> ((e & 1) * 16)) & 0xffffu);
-        else kx[e] = __uint_as_float(kw[c][e]);
-      }
+      const f32x4 kx = __builtin_bit_cast(f32x4, kw[c]);
 #pragma unroll
       for (int g = 0; g < G; ++g) {
+        const f32x4 qq = *reinterpret_cast<const f32x4*>(&s_q[g][4 * c]);
 #pragma unroll
-        for (int e4 = 0; e4 < EP / 4; ++e4) {
-          const f32x4 qq = *reinterpret_cast<const f32x4*>(&s_q[g][c * EP + 4 * e4]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) s[g] = fmaf(qq[e], kx[4 * e4 + e], s[g]);
-        }
+        for (int e = 0; e < 4; ++e) s[g] = fmaf(qq[e], kx[e], s[g]);
       }
-      // one piece at a time: its conversions and query reads stay with it
+      // one piece at a time: its query reads stay with it
       __builtin_amdgcn_sched_barrier(0);
     }
     // online softmax in log2 units; the maximum is uniform over the wave
@@ -445,12 +437,11 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
       const float alpha = exp2f(m[g] - mn);
       pr[g] = exp2f(sg - mn);
       l[g] = l[g] * alpha + pr[g];
-#pragma unroll
-      for (int e = 0; e < E; ++e) o[g][e] *= alpha;
+      o[g] *= alpha;
       m[g] = mn;
     }
     // P.V: the tile's V rows through LDS (row = key), then lane = head-dim
-    // slice reads each key's slice (consecutive lanes, consecutive words)
+    // element reads each key's (consecutive lanes, consecutive words)
     char* sv = s_v[wave];
 #pragma unroll
     for (int c = 0; c < NP; ++c) *reinterpret_cast<u32x4*>(sv + lane * VP + 16 * c) = vw[c];
@@ -458,19 +449,16 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
     const int nk = min(64, rs.R - tb);
 #pragma unroll 1
     for (int j0 = 0; j0 < nk; j0 += 8) {
-      float vv[8][E];
+      float vv[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int e = 0; e < E; ++e) vv[u][e] = load_elem<T, D>(sv + (j0 + u) * VP + (lane * E + e) * EB);
+      for (int u = 0; u < 8; ++u) vv[u] = load_f32(sv + (j0 + u) * VP + lane * 4);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         if (j0 + u < nk) {
 #pragma unroll
           for (int g = 0; g < G; ++g) {
             const float pj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pr[g]), j0 + u));
-#pragma unroll
-            for (int e = 0; e < E; ++e) o[g][e] = fmaf(pj, vv[u][e], o[g][e]);
+            o[g] = fmaf(pj, vv[u], o[g]);
           }
         }
       }
@@ -485,8 +473,7 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
       s_m[wave][g] = m[g];
       s_l[wave][g] = lt;
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e) s_o[wave][g][lane * E + e] = o[g][e];
+    s_o[wave][g][lane] = o[g];
   }
   __syncthreads();
   char* Ob = static_cast<char*>(a.Out);
@@ -503,9 +490,7 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
       den = fmaf(f, s_l[w][g], den);
     }
     const float out = num / den;
-    char* op = Ob + (row * a.out_tok + (int64_t)(h * G + g) * a.out_head + e) * EB;
-    if constexpr (EB == 2) *reinterpret_cast<uint16_t*>(op) = (uint16_t)float_to_bf16_bits(out);
-    else *reinterpret_cast<float*>(op) = out;
+    *reinterpret_cast<float*>(Ob + (row * a.out_tok + (int64_t)(h * G + g) * a.out_head + e) * 4) = out;
     if (a.o32) a.o32[(row * a.n_q_heads + h * G + g) * D + e] = out;
     if (e == 0) a.lse[row * a.n_q_heads + h * G + g] = (M + log2f(den)) * kLn2;
   }
@@ -1018,30 +1003,26 @@ hipError_t rows_fwd_mfma(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, int D>
-hipError_t rows_fwd_g(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
-  const dim3 grid((unsigned)(n_rows * a.n_kv_heads)), block(256);
-  if constexpr (Elem<T>::kBytes == 2) {
-    switch (a.gqa) {
-      case 1: return rows_fwd_mfma<D, 1>(a, n_rows, s);
-      case 2: return rows_fwd_mfma<D, 2>(a, n_rows, s);
-      case 4: return rows_fwd_mfma<D, 4>(a, n_rows, s);
-      default: return rows_fwd_mfma<D, 8>(a, n_rows, s);
-    }
-  } else {
-    switch (a.gqa) {
-      case 1: hipLaunchKernelGGL((attend_rows_fwd_kernel<T, D, 1>), grid, block, 0, s, a); break;
-      case 2: hipLaunchKernelGGL((attend_rows_fwd_kernel<T, D, 2>), grid, block, 0, s, a); break;
-      case 4: hipLaunchKernelGGL((attend_rows_fwd_kernel<T, D, 4>), grid, block, 0, s, a); break;
-      default: hipLaunchKernelGGL((attend_rows_fwd_kernel<T, D, 8>), grid, block, 0, s, a); break;
-    }
+template <int D>
+hipError_t rows_fwd_bf16(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
+  switch (a.gqa) {
+    case 1: return rows_fwd_mfma<D, 1>(a, n_rows, s);
+    case 2: return rows_fwd_mfma<D, 2>(a, n_rows, s);
+    case 4: return rows_fwd_mfma<D, 4>(a, n_rows, s);
+    default: return rows_fwd_mfma<D, 8>(a, n_rows, s);
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_attend_rows_fwd(const AttnArgs& a, int64_t n_rows, bool bf16, int head_dim, hipStream_t s) {
-  if (!bf16) return rows_fwd_g<float, 64>(a, n_rows, s);  // float32 is built for head_dim 64 only
-  return head_dim == 64 ? rows_fwd_g<__bf16, 64>(a, n_rows, s) : rows_fwd_g<__bf16, 128>(a, n_rows, s);
+  if (bf16) return head_dim == 64 ? rows_fwd_bf16<64>(a, n_rows, s) : rows_fwd_bf16<128>(a, n_rows, s);
+  const dim3 grid((unsigned)(n_rows * a.n_kv_heads)), block(256);
+  switch (a.gqa) {
+    case 1: hipLaunchKernelGGL(attend_rows_fwd_kernel<1>, grid, block, 0, s, a); break;
+    case 2: hipLaunchKernelGGL(attend_rows_fwd_kernel<2>, grid, block, 0, s, a); break;
+    case 4: hipLaunchKernelGGL(attend_rows_fwd_kernel<4>, grid, block, 0, s, a); break;
+    default: hipLaunchKernelGGL(attend_rows_fwd_kernel<8>, grid, block, 0, s, a); break;
+  }
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- backward
@@ -1061,40 +1042,29 @@ hipError_t launch_attend_rows_fwd(const AttnArgs& a, int64_t n_rows, bool bf16, 
 //                       for float32). No atomics: results are bitwise
 //                       reproducible.
 
-template <typename T, int D>
 __global__ __launch_bounds__(256) void rows_rowdot_kernel(AttnArgs a, int64_t n_rows) {
-  constexpr int EB = Elem<T>::kBytes;
-  constexpr int E = D / 64;
+  constexpr int D = 64;
   const int lane = threadIdx.x & 63;
   const int64_t x = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // (row, query head)
   if (x >= n_rows * a.n_q_heads) return;
   const int64_t row = x / a.n_q_heads;
   const int hq = (int)(x % a.n_q_heads);
-  const char* dob = static_cast<const char*>(a.dO) + (row * a.do_tok + (int64_t)hq * a.do_head) * EB;
-  float acc = 0.0f;
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int d = lane * E + e;
-    const float o = a.o32 ? a.o32[(row * a.n_q_heads + hq) * D + d]
-                          : load_elem<T, D>(static_cast<const char*>(a.O) +
-                                            (row * a.o_tok + (int64_t)hq * a.o_head + d) * EB);
-    acc = fmaf(load_elem<T, D>(dob + (int64_t)d * EB), o, acc);
-  }
-  acc = wave_sum(acc);
-  if (lane == 0) a.dvec[x] = acc;
+  const char* dob = static_cast<const char*>(a.dO) + (row * a.do_tok + (int64_t)hq * a.do_head) * 4;
+  const float o = a.o32 ? a.o32[x * D + lane]
+                        : load_f32(static_cast<const char*>(a.O) + (row * a.o_tok + (int64_t)hq * a.o_head + lane) * 4);
+  const float sum = wave_sum(fmaf(load_f32(dob + lane * 4), o, 0.0f));
+  if (lane == 0) a.dvec[x] = sum;
 }
 
 // float32 dQ on the vector units: the four waves stage each tile's K and V
 // rows together in LDS (double-buffered); each wave takes a query head,
 // forms dS (lane = key), then dQ = scale dS K (lane = head-dim slice, keys in
 // tile order).
-template <typename T, int D, int G>
+template <int G>
 __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
-  constexpr int EB = Elem<T>::kBytes;
-  constexpr int E = D / 64;             // dQ dims of a lane
-  constexpr int NP = D * EB / 16;       // 16-byte pieces of a key row
-  constexpr int EP = 16 / EB;           // elements per piece
-  constexpr int KP = D * EB + 16;       // LDS pitch of a staged K / V row (padded against bank conflicts)
+  constexpr int D = 64;                 // a lane per head-dim element of dQ
+  constexpr int NP = D / 4;             // 16-byte pieces of a key row
+  constexpr int KP = D * 4 + 16;        // LDS pitch of a staged K / V row (padded against bank conflicts)
   constexpr int HPW = (G + 3) / 4;      // query heads of a wave
   constexpr int PER = 2 * 64 * NP / 256;  // 16-byte pieces of a K/V tile per thread
   __shared__ __attribute__((aligned(16))) float s_q[G][D];
@@ -1112,8 +1082,8 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
   for (int x = tid; x < G * D; x += 256) {
     const int g = x / D, e = x % D;
     const int64_t hq = h * G + g;
-    s_q[g][e] = load_elem<T, D>(static_cast<const char*>(a.Q) + (row * a.q_tok + hq * a.q_head + e) * EB);
-    s_do[g][e] = load_elem<T, D>(static_cast<const char*>(a.dO) + (row * a.do_tok + hq * a.do_head + e) * EB);
+    s_q[g][e] = load_f32(static_cast<const char*>(a.Q) + (row * a.q_tok + hq * a.q_head + e) * 4);
+    s_do[g][e] = load_f32(static_cast<const char*>(a.dO) + (row * a.do_tok + hq * a.do_head + e) * 4);
   }
   if (tid < G) {
     s_lse[tid] = a.lse[row * a.n_q_heads + h * G + tid] * kLog2e;
@@ -1124,8 +1094,8 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
 
   // a tile's K and V rows: thread items (tensor, row, piece), all loads in
   // flight together, then stored to the tile's buffer
-  const int64_t k_stride = a.k_tok * EB, v_stride = a.v_tok * EB;
-  const int64_t k_head = (int64_t)h * a.k_head * EB, v_head = (int64_t)h * a.v_head * EB;
+  const int64_t k_stride = a.k_tok * 4, v_stride = a.v_tok * 4;
+  const int64_t k_head = (int64_t)h * a.k_head * 4, v_head = (int64_t)h * a.v_head * 4;
   auto fetch = [&](int tile, u32x4 (&st)[PER]) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
@@ -1154,11 +1124,9 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
   }
   __syncthreads();
 
-  float dq[HPW][E];
+  float dq[HPW];
 #pragma unroll
-  for (int i = 0; i < HPW; ++i)
-#pragma unroll
-    for (int e = 0; e < E; ++e) dq[i][e] = 0.0f;
+  for (int i = 0; i < HPW; ++i) dq[i] = 0.0f;
   for (int tile = 0; tile < ntiles; ++tile) {
     const int buf = tile & 1;
     u32x4 nx[PER];
@@ -1174,28 +1142,14 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
         float sg = 0.0f, dg = 0.0f;
 #pragma unroll 4
         for (int c = 0; c < NP; ++c) {
-          const u32x4 kw = *reinterpret_cast<const u32x4*>(sk + lane * KP + 16 * c);
-          const u32x4 vw = *reinterpret_cast<const u32x4*>(sv + lane * KP + 16 * c);
-          float kx[EP], vx[EP];
+          const f32x4 kx = *reinterpret_cast<const f32x4*>(sk + lane * KP + 16 * c);
+          const f32x4 vx = *reinterpret_cast<const f32x4*>(sv + lane * KP + 16 * c);
+          const f32x4 qq = *reinterpret_cast<const f32x4*>(&s_q[g][4 * c]);
+          const f32x4 dd = *reinterpret_cast<const f32x4*>(&s_do[g][4 * c]);
 #pragma unroll
-          for (int e = 0; e < EP; ++e) {
-            if constexpr (EB == 2) {
-              kx[e] = bf16_bits_to_float((kw[e >> 1] >> ((e & 1) * 16)) & 0xffffu);
-              vx[e] = bf16_bits_to_float((vw[e >> 1] >> ((e & 1) * 16)) & 0xffffu);
-            } else {
-              kx[e] = __uint_as_float(kw[e]);
-              vx[e] = __uint_as_float(vw[e]);
-            }
-          }
-#pragma unroll
-          for (int e4 = 0; e4 < EP / 4; ++e4) {
-            const f32x4 qq = *reinterpret_cast<const f32x4*>(&s_q[g][c * EP + 4 * e4]);
-            const f32x4 dd = *reinterpret_cast<const f32x4*>(&s_do[g][c * EP + 4 * e4]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              sg = fmaf(qq[e], kx[4 * e4 + e], sg);
-              dg = fmaf(dd[e], vx[4 * e4 + e], dg);
-            }
+          for (int e = 0; e < 4; ++e) {
+            sg = fmaf(qq[e], kx[e], sg);
+            dg = fmaf(dd[e], vx[e], dg);
           }
         }
         const float pr = lane < nk ? exp2f(sg * a.scale_log2 - s_lse[g]) : 0.0f;
@@ -1203,17 +1157,13 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
       }
     }
     __builtin_amdgcn_wave_barrier();  // a wave reads only the dS rows it wrote
-    // dQ += dS K: lane = head-dim slice, keys of the tile in order
+    // dQ += dS K: lane = head-dim element, keys of the tile in order
 #pragma unroll
     for (int i = 0; i < HPW; ++i) {
       const int g = wave + 4 * i;
       if (g < G) {
 #pragma unroll 8
-        for (int j = 0; j < nk; ++j) {
-          const float dj = s_ds[g][j];
-#pragma unroll
-          for (int e = 0; e < E; ++e) dq[i][e] = fmaf(dj, load_elem<T, D>(sk + j * KP + (lane * E + e) * EB), dq[i][e]);
-        }
+        for (int j = 0; j < nk; ++j) dq[i] = fmaf(s_ds[g][j], load_f32(sk + j * KP + lane * 4), dq[i]);
       }
     }
     if (tile + 1 < ntiles) {
@@ -1226,10 +1176,7 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
 #pragma unroll
   for (int i = 0; i < HPW; ++i) {
     const int g = wave + 4 * i;
-    if (g < G) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) a.dQ[(row * a.n_q_heads + h * G + g) * D + lane * E + e] = dq[i][e] * a.scale;
-    }
+    if (g < G) a.dQ[(row * a.n_q_heads + h * G + g) * D + lane] = dq[i] * a.scale;
   }
 }
 
@@ -1245,8 +1192,8 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
 // workgroup per row, one lane per key) + 8.8 us (D, a kernel of its own)
 // before, 57 us in all so.
 template <int D, int G, int RPW, int KW>
-__global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void rows_dq_mfma_kernel(AttnArgs a,
-                                                                                     int64_t n_rows, int64_t n_groups) {
+__global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void
+rows_dq_mfma_kernel(AttnArgs a, int64_t n_rows, int64_t n_groups) {
   using TL = Tile<__bf16, D>;
   constexpr int NS = D / 32;       // k steps of S and dP
   constexpr int NT = D / 16;       // 16-row tiles of dQ^T
@@ -1427,7 +1374,8 @@ __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_wave
         const int p = x / (D / 4), d0 = 4 * (x % (D / 4));
         f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int w = 0; w < KW; ++w) v += *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(s_kv[w]) + p * D + d0);
+        for (int w = 0; w < KW; ++w)
+          v += *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(s_kv[w]) + p * D + d0);
         *reinterpret_cast<f32x4*>(a.dQ + ((row0 + p / G) * a.n_q_heads + h * G + p % G) * D + d0) = v * a.scale;
       }
       __syncthreads();  // the buffers are read: a further pass may overwrite them
@@ -1506,14 +1454,13 @@ __device__ inline int rows_attending(const AttnArgs& a, int64_t n_rows, int h, i
 // time; the waves split the (row, query head) pairs for S and dP (lane = key
 // and a quarter of the head dim, quarters added across lanes), share P and dS
 // through LDS, and each thread accumulates a slice of dK and dV for one key.
-template <typename T, int D, int G>
+template <int G>
 __global__ __launch_bounds__(256) void rows_dkv_kernel(AttnArgs a, int64_t n_rows) {
-  constexpr int EB = Elem<T>::kBytes;
+  constexpr int D = 64;
   constexpr int KW = kRowsDkvKeys;     // keys of this workgroup
   constexpr int NQ = 64 / KW;          // lanes per key: head-dim parts of a dot product
   constexpr int DQ = D / NQ;           // head dims of one part
-  constexpr int NPQ = DQ * EB / 16;    // 16-byte pieces of one part of a row
-  constexpr int EP = 16 / EB;
+  constexpr int NPQ = DQ / 4;          // 16-byte pieces of one part of a row
   constexpr int DE = DQ / 4;           // dK / dV dims a thread accumulates
   __shared__ int s_rows[kRowsBwdMaxRows];  // the row lists live in LDS: calls of at most this many rows
   __shared__ uint32_t s_mask[kRowsBwdMaxRows];
@@ -1538,8 +1485,8 @@ __global__ __launch_bounds__(256) void rows_dkv_kernel(AttnArgs a, int64_t n_row
   // ---- this lane's key and head-dim part for the dot products
   const int kk = lane % KW, qd = lane / KW;
   const int64_t tk = min(k0 + kk, q_end - 1);  // keys past the call's end are never attended
-  const char* kr = row_ptr(static_cast<const char*>(a.K), tk, a.k_tok * EB) + ((int64_t)h * a.k_head + qd * DQ) * EB;
-  const char* vr = row_ptr(static_cast<const char*>(a.V), tk, a.v_tok * EB) + ((int64_t)h * a.v_head + qd * DQ) * EB;
+  const char* kr = row_ptr(static_cast<const char*>(a.K), tk, a.k_tok * 4) + ((int64_t)h * a.k_head + qd * DQ) * 4;
+  const char* vr = row_ptr(static_cast<const char*>(a.V), tk, a.v_tok * 4) + ((int64_t)h * a.v_head + qd * DQ) * 4;
   u32x4 kw[NPQ], vw[NPQ];
 #pragma unroll
   for (int p = 0; p < NPQ; ++p) kw[p] = *reinterpret_cast<const u32x4*>(kr + 16 * p);
@@ -1567,8 +1514,8 @@ __global__ __launch_bounds__(256) void rows_dkv_kernel(AttnArgs a, int64_t n_row
       st[u] = 0.0f;
       if (x < NV)
         st[u] = which == 0
-            ? load_elem<T, D>(static_cast<const char*>(a.Q) + (rr * a.q_tok + hq * a.q_head + e) * EB)
-            : load_elem<T, D>(static_cast<const char*>(a.dO) + (rr * a.do_tok + hq * a.do_head + e) * EB);
+            ? load_f32(static_cast<const char*>(a.Q) + (rr * a.q_tok + hq * a.q_head + e) * 4)
+            : load_f32(static_cast<const char*>(a.dO) + (rr * a.do_tok + hq * a.do_head + e) * 4);
     }
   };
   auto stage = [&](int kb, int buf, const float (&st)[PER]) {
@@ -1610,26 +1557,13 @@ __global__ __launch_bounds__(256) void rows_dkv_kernel(AttnArgs a, int64_t n_row
         float s = 0.0f, dp = 0.0f;
 #pragma unroll
         for (int p = 0; p < NPQ; ++p) {
-          float kx[EP], vx[EP];
+          const f32x4 kx = __builtin_bit_cast(f32x4, kw[p]), vx = __builtin_bit_cast(f32x4, vw[p]);
+          const f32x4 qq = *reinterpret_cast<const f32x4*>(&s_q[buf][r][g][qd * DQ + 4 * p]);
+          const f32x4 dd = *reinterpret_cast<const f32x4*>(&s_do[buf][r][g][qd * DQ + 4 * p]);
 #pragma unroll
-          for (int e = 0; e < EP; ++e) {
-            if constexpr (EB == 2) {
-              kx[e] = bf16_bits_to_float((kw[p][e >> 1] >> ((e & 1) * 16)) & 0xffffu);
-              vx[e] = bf16_bits_to_float((vw[p][e >> 1] >> ((e & 1) * 16)) & 0xffffu);
-            } else {
-              kx[e] = __uint_as_float(kw[p][e]);
-              vx[e] = __uint_as_float(vw[p][e]);
-            }
-          }
-#pragma unroll
-          for (int e4 = 0; e4 < EP / 4; ++e4) {
-            const f32x4 qq = *reinterpret_cast<const f32x4*>(&s_q[buf][r][g][qd * DQ + p * EP + 4 * e4]);
-            const f32x4 dd = *reinterpret_cast<const f32x4*>(&s_do[buf][r][g][qd * DQ + p * EP + 4 * e4]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              s = fmaf(qq[e], kx[4 * e4 + e], s);
-              dp = fmaf(dd[e], vx[4 * e4 + e], dp);
-            }
+          for (int e = 0; e < 4; ++e) {
+            s = fmaf(qq[e], kx[e], s);
+            dp = fmaf(dd[e], vx[e], dp);
           }
         }
 #pragma unroll
@@ -1843,50 +1777,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void r
   }
 }
 
-template <typename T, int D, int G>
-hipError_t rows_bwd_g(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
-  const int64_t q_end = a.q_begin + n_rows;
-  const int n_act = (int)((q_end - a.grad_begin + 63) / 64);
-  if constexpr (Elem<T>::kBytes == 2) {
-    constexpr int R = rows_per_group<G>();
-    const int64_t ng = n_row_groups(a, n_rows, R);
-    const dim3 each((unsigned)(n_rows * a.n_kv_heads));
-    if (ng * a.n_kv_heads >= kRowsWaveGroups)
-      hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 1>), dim3((unsigned)((ng + 3) / 4 * a.n_kv_heads)), dim3(256),
-                         0, s, a, n_rows, ng);
-    else if (!rows_apart(a, n_rows, R, 512))
-      hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 4>), dim3((unsigned)(ng * a.n_kv_heads)), dim3(256), 0, s, a,
-                         n_rows, ng);
-    else if (many_waves(a, n_rows, 16))
-      hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, 1, 8>), each, dim3(512), 0, s, a, n_rows, n_rows);
-    else
-      hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, 1, 4>), each, dim3(256), 0, s, a, n_rows, n_rows);
-  } else {
-    const int64_t pairs = n_rows * a.n_q_heads;
-    hipLaunchKernelGGL((rows_rowdot_kernel<T, D>), dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, s, a, n_rows);
-    hipLaunchKernelGGL((rows_dq_kernel<T, D, G>), dim3((unsigned)(n_rows * a.n_kv_heads)), dim3(256), 0, s, a);
-  }
-  const dim3 dkv_grid((unsigned)(n_act * a.n_kv_heads * (64 / kRowsDkvKeys)));
-  if constexpr (Elem<T>::kBytes == 2)
-    hipLaunchKernelGGL((rows_dkv_mfma_kernel<D, G>), dkv_grid, dim3(256), 0, s, a, n_rows);
+// Workgroups of the dK/dV kernels: 16 keys of an active chunk, kv head.
+static dim3 rows_dkv_grid(const AttnArgs& a, int64_t n_rows) {
+  const int n_act = (int)((a.q_begin + n_rows - a.grad_begin + 63) / 64);
+  return dim3((unsigned)(n_act * a.n_kv_heads * (64 / kRowsDkvKeys)));
+}
+
+template <int D, int G>
+hipError_t rows_bwd_mfma(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
+  constexpr int R = rows_per_group<G>();
+  const int64_t ng = n_row_groups(a, n_rows, R);
+  const dim3 each((unsigned)(n_rows * a.n_kv_heads));
+  if (ng * a.n_kv_heads >= kRowsWaveGroups)
+    hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 1>), dim3((unsigned)((ng + 3) / 4 * a.n_kv_heads)), dim3(256), 0,
+                       s, a, n_rows, ng);
+  else if (!rows_apart(a, n_rows, R, 512))
+    hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 4>), dim3((unsigned)(ng * a.n_kv_heads)), dim3(256), 0, s, a,
+                       n_rows, ng);
+  else if (many_waves(a, n_rows, 16))
+    hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, 1, 8>), each, dim3(512), 0, s, a, n_rows, n_rows);
   else
-    hipLaunchKernelGGL((rows_dkv_kernel<T, D, G>), dkv_grid, dim3(256), 0, s, a, n_rows);
+    hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, 1, 4>), each, dim3(256), 0, s, a, n_rows, n_rows);
+  hipLaunchKernelGGL((rows_dkv_mfma_kernel<D, G>), rows_dkv_grid(a, n_rows), dim3(256), 0, s, a, n_rows);
   return hipGetLastError();
 }
 
-template <typename T, int D>
-hipError_t rows_bwd_d(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
+template <int D>
+hipError_t rows_bwd_bf16(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
   switch (a.gqa) {
-    case 1: return rows_bwd_g<T, D, 1>(a, n_rows, s);
-    case 2: return rows_bwd_g<T, D, 2>(a, n_rows, s);
-    case 4: return rows_bwd_g<T, D, 4>(a, n_rows, s);
-    default: return rows_bwd_g<T, D, 8>(a, n_rows, s);
+    case 1: return rows_bwd_mfma<D, 1>(a, n_rows, s);
+    case 2: return rows_bwd_mfma<D, 2>(a, n_rows, s);
+    case 4: return rows_bwd_mfma<D, 4>(a, n_rows, s);
+    default: return rows_bwd_mfma<D, 8>(a, n_rows, s);
   }
 }
 
+template <int G>
+hipError_t rows_bwd_f32(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
+  const int64_t pairs = n_rows * a.n_q_heads;
+  hipLaunchKernelGGL(rows_rowdot_kernel, dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, s, a, n_rows);
+  hipLaunchKernelGGL(rows_dq_kernel<G>, dim3((unsigned)(n_rows * a.n_kv_heads)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(rows_dkv_kernel<G>, rows_dkv_grid(a, n_rows), dim3(256), 0, s, a, n_rows);
+  return hipGetLastError();
+}
+
 hipError_t launch_attend_rows_bwd(const AttnArgs& a, int64_t n_rows, bool bf16, int head_dim, hipStream_t s) {
-  if (!bf16) return rows_bwd_d<float, 64>(a, n_rows, s);  // float32 is built for head_dim 64 only
-  return head_dim == 64 ? rows_bwd_d<__bf16, 64>(a, n_rows, s) : rows_bwd_d<__bf16, 128>(a, n_rows, s);
+  if (bf16) return head_dim == 64 ? rows_bwd_bf16<64>(a, n_rows, s) : rows_bwd_bf16<128>(a, n_rows, s);
+  switch (a.gqa) {
+    case 1: return rows_bwd_f32<1>(a, n_rows, s);
+    case 2: return rows_bwd_f32<2>(a, n_rows, s);
+    case 4: return rows_bwd_f32<4>(a, n_rows, s);
+    default: return rows_bwd_f32<8>(a, n_rows, s);
+  }
 }
 
 }  // namespace hga
