@@ -435,9 +435,13 @@ static hipError_t fwd_dispatch(const AttnArgs& a, hipStream_t s) {
   // four query heads per workgroup share each gathered tile; with fewer
   // (block, kv head) pairs than the chip has CUs, two heads per workgroup
   // fill it instead. bf16 with d = 64 takes two heads always: three such
-  // workgroups fit a CU and hide each other's start and end (10,048 queries,
-  // G = 8: 50 us against 60 with four heads and one workgroup per CU; at
-  // d = 128, where two fit, 131,072 queries took 1,759 against 1,590).
+  // workgroups fit a CU and hide each other's start and end, which outweighs
+  // gathering each tile twice and a few spilled registers (us with two heads
+  // and, before, four heads and one workgroup per CU: 10,048 queries, G = 8,
+  // 320 keys 53 and 65, 1,216 keys 139 and 163, 4,352 keys 339 and 407; 40,000
+  // queries 202 and 256; with o_f32 77 and 81; 2,048 queries 14 and 16, with
+  // o_f32 20 and 20). At d = 128, where two fit, 131,072 queries took 1,759
+  // against 1,590.
   int gw = a.gqa >= 4 ? 4 : a.gqa;
   if (gw == 4 && three_per_simd<T, D, 2>()) gw = 2;
   if (gw == 4 && (int64_t)a.n_qb * a.n_kv_heads * (a.gqa / 4) < 256) gw = 2;

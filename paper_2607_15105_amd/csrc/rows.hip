@@ -533,10 +533,13 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
 // workgroup per row and one lane per key, 50 us so; a decode step at 16K 9.6 and
 // 7.1 us.
 constexpr int kRowsStep = 32;  // keys of a step
-// Which form a call takes. A wave per group from 1,024 (group, kv head) pairs on
-// (Qwen3-8B layer, 320 keys a row: 256 rows, 512 group pairs, take 27.8 us so and
-// 19.2 with four waves, 512 rows 29.9 and 33.7, 1,024 rows 50 and 61); below,
-// rows on their own while they are few, else four waves per group.
+// Which form a call takes. A wave per group from 1,024 (group, kv head) pairs on;
+// below, rows on their own while they are few, else four waves per group. (Qwen3-8B
+// layer, forward, a wave and four per group, us: 320 keys a row, 256 rows or 512
+// group pairs 32 and 20, 512 rows 31 and 33, 768 43 and 47, 1,024 46 and 61. The line
+// is for such lists: of 96 keys 320 rows take 12.7 and 14.9, of 1,216 keys 512 rows
+// 166 and 139, 768 228 and 204, 1,024 243 and 266; at d = 64 512 rows 22 and 17,
+// 1,024 28 and 30.)
 constexpr int64_t kRowsWaveGroups = 1024;
 
 // The keys of the last row's block in the windows, and those of a row's
