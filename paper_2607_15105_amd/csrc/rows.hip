@@ -107,11 +107,11 @@ struct RowsRoute {
 // sixteenth of the round (contiguous, so that kept positions stay in chunk
 // order); wave 0 then selects from the kept entries of all. (Decode step at
 // 131K, 2,027 candidates: 34 us with four waves and one selection by ranks,
-// 23 us so. The scoring takes half of it: the CU's float64 conversions and the
+// 20 us so. The scoring takes half of it: the CU's float64 conversions and the
 // descriptor's LDS reads, not the summary rows; four load slots were no faster.)
 // WHOLE (one row, 256 threads): a summary row's loads all in flight at once, one
 // workgroup per CU. It is the shortest for a workgroup on its own, so it serves
-// calls with at most one per CU (one row at 16K: 9.3 us against 12.8 with ranks);
+// calls with at most one per CU (one row at 16K: 9.9 us against 12.8 with ranks);
 // with more, the sixteen-element units let four share a CU (64 rows at 16K,
 // 512 workgroups: 18 us whole, 10.9 in units; 15.4 with ranks).
 template <typename T, int D, int RB, int NT, bool WHOLE>
@@ -530,8 +530,8 @@ __global__ __launch_bounds__(256) void attend_rows_fwd_kernel(AttnArgs a) {
 // row's, where RPW == 1) and merge their softmax states through LDS.
 //
 // Strictly causal 1,024-row segment at 16K (Qwen3-8B layer): 172 us with one
-// workgroup per row and one lane per key, 50 us so; a decode step at 16K 9.6 and
-// 7.1 us.
+// workgroup per row and one lane per key, 46 us so; a decode step at 16K 9.6 and
+// 6.8 us.
 constexpr int kRowsStep = 32;  // keys of a step
 // Which form a call takes. A wave per group from 1,024 (group, kv head) pairs on;
 // below, rows on their own while they are few, else four waves per group. (Qwen3-8B
@@ -1193,7 +1193,7 @@ __global__ __launch_bounds__(256) void rows_dq_kernel(AttnArgs a) {
 //
 // Strictly causal 1,024-row segment at 16K (Qwen3-8B layer): 255 us (dQ, one
 // workgroup per row, one lane per key) + 8.8 us (D, a kernel of its own)
-// before, 57 us in all so.
+// before, 53 us in all so.
 template <int D, int G, int RPW, int KW>
 __global__ __launch_bounds__(KW == 1 ? 256 : 64 * KW) __attribute__((amdgpu_waves_per_eu(2))) void
 rows_dq_mfma_kernel(AttnArgs a, int64_t n_rows, int64_t n_groups) {
