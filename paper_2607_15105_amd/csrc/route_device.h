@@ -18,8 +18,6 @@
 // score first, lower index on equal scores (NaN scores count as -inf); the
 // selected sets are returned ascending.
 #pragma once
-#include <type_traits>
-
 #include "hga_device.h"
 #include "hga_kernels.h"
 
@@ -191,18 +189,16 @@ __device__ inline int rank_select(TopKScratch& ws, int L, int k_eff, int lane) {
 // k entries, so every top-k entry is at or above it too. The entries at or
 // above the threshold are compacted in index order (at most k lane slices
 // contribute, so n <= 256 always fits kListCap) and ranked exactly: an
-// entry's rank among them equals its rank among all n.
-__device__ __attribute__((always_inline)) inline int wave_top_k_ranked(const double* sc, int n, int k,
-                                                                       int lane, TopKScratch& ws) {
-  const int k_eff = min(k, n);
-  if (k_eff <= 0) return kNoIdx;
-  if (k_eff == n) return lane < n ? lane : kNoIdx;  // take all (n <= 64)
-  int L;
+// entry's rank among them equals its rank among all n. too_long: the list is
+// known not to fit.
+__device__ __attribute__((always_inline)) inline int wave_top_k_ranked(const double* sc, int n, int k_eff, int lane,
+                                                                       TopKScratch& ws, bool too_long) {
+  int L = kListCap + 1;
   if (n <= 64) {
     ws.lv[lane] = lane < n ? sc[lane] : -__builtin_inf();
     ws.li[lane] = lane < n ? lane : kNoIdx;
     L = n;
-  } else {
+  } else if (!too_long) {
     double bv = -__builtin_inf();
     int bi = kNoIdx;
     for (int i0 = lane; i0 < n; i0 += 256) {
@@ -240,9 +236,9 @@ __device__ __attribute__((always_inline)) inline int wave_top_k_ranked(const dou
         base += __popcll(mq);
       }
     }
-    if (base > kListCap) return top_k_tournament(sc, n, k_eff, lane);
     L = base;
   }
+  if (L > kListCap) return top_k_tournament(sc, n, k_eff, lane);
   __builtin_amdgcn_wave_barrier();
   // rank of each list entry; this lane holds entries lane + 64 e
   int nsel = 0;
@@ -374,7 +370,7 @@ __device__ __attribute__((always_inline)) inline int wave_top_k(const double* sc
   const int k_eff = min(k, n);
   if (k_eff <= 0) return kNoIdx;
   if (k_eff == n) return lane < n ? lane : kNoIdx;  // take all (n <= 64)
-  bool done = false;
+  bool done = false, too_long = false;
   if (n <= 64) {
     done = top_k_keys<1>(sc, nullptr, n, k_eff, lane, ws);
   } else if (n <= 256) {
@@ -396,49 +392,43 @@ __device__ __attribute__((always_inline)) inline int wave_top_k(const double* sc
       T = wave_min_u32(best[0]);
       tied = __popcll(__ballot(best[0] == T)) > 1;
     }
-    // the entries at or above T to the list, in order; FEW: of the ties at T,
-    // which must be equal, the first k
+    // the entries at or above T to the list, in order; where maxima tie, of the
+    // scores at T, which must be equal, the first k
     double tv = 0.0;
-    int n_ties = 0;
+    int L = 0, n_ties = 0;
     bool mixed = false;
-    auto cut = [&](auto few) __attribute__((always_inline)) {
-      constexpr bool FEW = decltype(few)::value;
-      int L = 0;
-      for (int j0 = 0; j0 < n; j0 += 256) {
-        double v[4];
+    for (int j0 = 0; j0 < n; j0 += 256) {
+      double v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = sc[min(j0 + 64 * u + lane, n - 1)];
+      for (int u = 0; u < 4; ++u) v[u] = sc[min(j0 + 64 * u + lane, n - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int p = j0 + 64 * u + lane;
-          bool q = (p < n) & (score_key(v[u]) >= T);
-          if constexpr (FEW) {
-            const bool tie = q & (score_key(v[u]) == T);
-            const uint64_t m = __ballot(tie);
-            if (m && n_ties == 0) tv = readlane_d(v[u], __builtin_ctzll(m));
-            mixed |= __ballot(tie && v[u] != tv) != 0;
-            q &= !tie | (n_ties + lanes_below(m) < k_eff);
-            n_ties += __popcll(m);
-          }
-          const uint64_t m = __ballot(q);
-          const int pos = L + lanes_below(m);
-          if (q && pos < kListCap) {
-            ws.lv[pos] = v[u];
-            ws.li[pos] = p;
-          }
-          L += __popcll(m);
+      for (int u = 0; u < 4; ++u) {
+        const int p = j0 + 64 * u + lane;
+        bool q = (p < n) & (score_key(v[u]) >= T);
+        if (__builtin_expect(tied, 0)) {
+          const bool tie = q & (score_key(v[u]) == T);
+          const uint64_t m = __ballot(tie);
+          if (m && n_ties == 0) tv = readlane_d(v[u], __builtin_ctzll(m));
+          mixed |= __ballot(tie && v[u] != tv) != 0;
+          q &= !tie | (n_ties + lanes_below(m) < k_eff);
+          n_ties += __popcll(m);
         }
+        const uint64_t m = __ballot(q);
+        const int pos = L + lanes_below(m);
+        if (q && pos < kListCap) {
+          ws.lv[pos] = v[u];
+          ws.li[pos] = p;
+        }
+        L += __popcll(m);
       }
-      return L;
-    };
-    const int L = __builtin_expect(tied, 0) ? cut(std::true_type{}) : cut(std::false_type{});
-    if (__builtin_expect(mixed, 0)) return wave_top_k_ranked(sc, n, k, lane, ws);
-    if (__builtin_expect(L > kListCap, 0)) return top_k_tournament(sc, n, k_eff, lane);
+    }
+    too_long = !mixed && L > kListCap;
     __builtin_amdgcn_wave_barrier();
-    if (L <= 64) done = top_k_keys<1>(ws.lv, ws.li, L, k_eff, lane, ws);
+    if (__builtin_expect(mixed | too_long, 0)) done = false;
+    else if (L <= 64) done = top_k_keys<1>(ws.lv, ws.li, L, k_eff, lane, ws);
     else done = top_k_keys<4>(ws.lv, ws.li, L, k_eff, lane, ws);
   }
-  if (__builtin_expect(!done, 0)) return wave_top_k_ranked(sc, n, k, lane, ws);
+  if (__builtin_expect(!done, 0)) return wave_top_k_ranked(sc, n, k_eff, lane, ws, too_long);
   return lane < k_eff ? ws.out[lane] : kNoIdx;
 }
 
