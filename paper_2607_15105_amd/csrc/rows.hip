@@ -566,13 +566,14 @@ static bool rows_apart(const AttnArgs& a, int64_t n_rows, int rpw, int64_t most)
   return pairs <= 256 || (pairs <= most && window_keys(a, n_rows) < (2 * rpw - 3) * private_keys(a));
 }
 
-// Waves for a row on its own: four, or `many` where it has a CU to itself and
-// more than `steps` steps to walk (one row, forward: 320 keys 7.5 us with four
-// and 8.0 with twelve, 576 9.8 and 10.0, 704 11.0 and 11.0, 1,216 15.9 and 13.7;
-// dQ: 320 keys 13.8 with four and 14.3 with eight, 576 16.1 and 15.9, 1,216 22.7
-// and 20.8).
-static bool many_waves(const AttnArgs& a, int64_t n_rows, int64_t steps) {
-  return n_rows * a.n_kv_heads <= 256 && window_keys(a, n_rows) + private_keys(a) > steps * kRowsStep;
+// Waves for a row on its own: four, or many (twelve, dQ eight) where it has a CU
+// to itself and more than sixteen steps to walk. (One row, the same inputs again
+// and again: forward, 320 keys 7.5 us with four and 8.0 with twelve, 576 9.8 and
+// 10.0, 704 11.0 and 11.0, 1,216 15.9 and 13.7; dQ with the rest, 320 keys 13.8
+// with four and 14.3 with eight, 576 16.1 and 15.9, 1,216 22.7 and 20.8. A decode
+// step at 131K with inputs that change, 576 keys: 33.7 and 33.3.)
+static bool many_waves(const AttnArgs& a, int64_t n_rows) {
+  return n_rows * a.n_kv_heads <= 256 && window_keys(a, n_rows) + private_keys(a) > 16 * kRowsStep;
 }
 
 // Maximum and sum over the four lanes l % 16 + 16 i, the same in each.
@@ -996,7 +997,7 @@ hipError_t rows_fwd_mfma(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
   } else if (!rows_apart(a, n_rows, R, 640)) {
     hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, R, 4>), dim3((unsigned)(ng * a.n_kv_heads)), dim3(256), 0,
                        s, a, n_rows, ng);
-  } else if (many_waves(a, n_rows, 24)) {
+  } else if (many_waves(a, n_rows)) {
     hipLaunchKernelGGL((attend_rows_fwd_mfma_kernel<D, G, 1, 12>), dim3((unsigned)(n_rows * a.n_kv_heads)),
                        dim3(768), 0, s, a, n_rows, n_rows);
   } else {
@@ -1797,7 +1798,7 @@ hipError_t rows_bwd_mfma(const AttnArgs& a, int64_t n_rows, hipStream_t s) {
   else if (!rows_apart(a, n_rows, R, 512))
     hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, R, 4>), dim3((unsigned)(ng * a.n_kv_heads)), dim3(256), 0, s, a,
                        n_rows, ng);
-  else if (many_waves(a, n_rows, 16))
+  else if (many_waves(a, n_rows))
     hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, 1, 8>), each, dim3(512), 0, s, a, n_rows, n_rows);
   else
     hipLaunchKernelGGL((rows_dq_mfma_kernel<D, G, 1, 4>), each, dim3(256), 0, s, a, n_rows, n_rows);

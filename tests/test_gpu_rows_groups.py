@@ -167,7 +167,7 @@ def test_rows_float32_output_keeps_the_weights(n_q, tails):
 @pytest.mark.parametrize("n_q,q_begin", [(1, 1787), (33, 1503)])
 @pytest.mark.parametrize("G,d", [(1, 128), (4, 64), (4, 128), (8, 128)])
 def test_rows_long_lists(G, d, n_q, q_begin):
-    """More than 24 steps of 32 keys a row, few rows: twelve waves per row, and
+    """More than 16 steps of 32 keys a row, few rows: twelve waves per row, and
     eight for dQ up to 256 pairs; with 264 pairs four."""
     wl = synth.Workload("rows_long", T=2048, n_q_heads=8 * G, n_kv_heads=8, head_dim=d, dtype="bf16", seed=37,
                         q_begin=q_begin, n_q=n_q, grad_begin=q_begin // 64 * 64 - 64, key_offset="normal",
