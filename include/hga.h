@@ -262,8 +262,9 @@ hga_status_t hga_attend_gathered_fwd(const hga_config_t* cfg, const void* Q, hga
  * computes dQ (query-major) and dK/dV (key-major) side by side. dK/dV are
  * accumulated in fixed order (no atomics; the split partials are summed in a
  * fixed order by a third kernel): results are bitwise reproducible run to
- * run, for the same number of subsets. With bf16 inputs dS enters dQ = dS K as a pair of bf16 values
- * (hi + lo), since dQ scales dS by raw key magnitudes.
+ * run, for the same number of subsets. With bf16 inputs dS enters dQ = dS K
+ * as a pair of bf16 values (hi + lo), since dQ scales dS by raw key
+ * magnitudes.
  */
 hga_status_t hga_attend_bwd(const hga_config_t* cfg, const void* Q, hga_strides_t qs,
                             const void* K, hga_strides_t ks, const void* V, hga_strides_t vs,
